@@ -236,7 +236,12 @@ int mf_tune_info(const mf_operator* op, int nvec, int prec, int* cfg, double* ms
  *                LDS buffers) even on axis-aligned cells; it cannot be undone
  *                on this operator.
  *   cfg          launch shape of the axis-aligned-cell kernel, 0..12, or -1
- *                for the built-in choice by column count.  Shapes 2 and 4 give
+ *                for the built-in choice by column count and mesh.  Shape 0
+ *                holds a cell of up to 16 columns in the registers of one
+ *                wavefront that marches along y (q <= 7; other calls, and
+ *                multivectors that span 3.75 GiB or more or a deterministic
+ *                assembly, run the box kernel's default shape instead).
+ *                Shapes 2 and 4 give
  *                every thread two adjacent columns (16-byte accesses); a call
  *                with odd nvec, odd ldx or ldy, or X or Y not 16-byte aligned
  *                runs the one-column shape with the same tile instead.

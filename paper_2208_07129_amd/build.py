@@ -57,6 +57,10 @@ def jobs():
     for p in range(1, MAX_P + 1):
         out.append(("apply_f64.hip", f"apply_f64_p{p}.o", [f"-DMF_P={p}"]))
         out.append(("apply_box.hip", f"apply_box_p{p}.o", [f"-DMF_P={p}"]))
+        if p <= 6:
+            # matrix-core results straight in the vector registers that read them
+            out.append(("apply_pair.hip", f"apply_pair_p{p}.o",
+                        [f"-DMF_P={p}", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]))
         if p <= 7:
             out.append(("apply_mfma.hip", f"apply_mfma_p{p}.o", [f"-DMF_P={p}"]))
         out.append(("apply_mixed.hip", f"apply_mixed_p{p}.o", [f"-DMF_P={p}"]))

@@ -420,6 +420,7 @@ int mf::apply_dispatch(mf_operator* handle, const double* X, double* Y, int nvec
   a.threads = 256;
   a.vtile = choose_vtile_f64(op->np, op->nq, nvec);
   a.cfg = mixed ? op->mcfg : op->cfg;
+  bool pair_asked = !mixed && a.cfg == 0;
   if (a.cfg < 0) {
     const auto it = op->tuned.find({prec, nvec});
     if (it != op->tuned.end())
@@ -427,7 +428,16 @@ int mf::apply_dispatch(mf_operator* handle, const double* X, double* Y, int nvec
     else
       a.cfg = mixed ? choose_cfg_mixed(op->np, op->nq, nvec, prec)
                     : choose_cfg_box(op->np, op->nq, nvec);
+    if (!mixed)
+      pair_asked = it != op->tuned.end() ? it->second == 0 : pair_chosen(*op, nvec);
   }
+  // Shape 0 is the register-resident form where it is built, its 32-bit offsets
+  // reach the multivectors and the assembly is atomic; else a box kernel shape.
+  PairPlan plan{};
+  if (pair_asked && op->box && !op->deterministic && pair_built(op->q) &&
+      xb < (size_t)kPairMaxSpan && yb < (size_t)kPairMaxSpan)
+    plan = pair_plan(*op, nvec);
+  const bool pair = plan.items > 0;
   if (mixed && a.cfg >= kMixedMfmaCfgs && !box_pairs_ok(X, Y, nvec, ldx, ldy))
     a.cfg = vec32_cfg_single(a.cfg);
   if (!mixed && op->box && !box_pairs_ok(X, Y, nvec, ldx, ldy))
@@ -444,14 +454,16 @@ int mf::apply_dispatch(mf_operator* handle, const double* X, double* Y, int nvec
   hipError_t err = hipSuccess;
   if (!accumulate) {
     // the box kernels store cell-interior rows and add to the others
-    err = op->box       ? launch_zero_shared_rows(Y, op->nodes, op->p, nvec, ldy, s)
+    err = op->box       ? launch_zero_shared_rows(Y, op->nodes, op->p,
+                                                  pair ? op->p * plan.len : op->p, nvec, ldy, s)
         : op->map_box ? launch_zero_listed_rows(Y, op->d_zrows, op->nzrows, nvec, ldy, s)
                       : launch_zero_rows(Y, op->ndofs, nvec, ldy, s);
     if (err != hipSuccess) return hip_fail(err, "zero kernel launch");
   }
   if (ev) (void)hipEventRecord(ev[1], s);
   auto launch = [&]() {
-    return map32   ? launch_apply_box_map32(*op, a, s)
+    return pair    ? launch_apply_pair(*op, a, plan, s)
+           : map32 ? launch_apply_box_map32(*op, a, s)
            : mixed ? launch_apply_mixed(*op, a, prec, s)
                  : (op->box       ? (a.cfg == kBoxMfmaCfg ? launch_apply_mfma(*op, a, s)
                                                             : launch_apply_box(*op, a, s))

@@ -49,20 +49,21 @@ __global__ void __launch_bounds__(256) fma_probe_kernel(int64_t iters, double se
 
 // Node lines (gy, gz) of the Nx x Ny x Nz grid, each taken whole by one
 // workgroup (a grid-stride loop when the grid is smaller than the line count).
-// A line on a cell-face plane (gy or gz a multiple of p) is zeroed whole;
-// otherwise only the rows gx = 0, p, 2p, ... are.  Threads form (row, column)
+// A line on a shared plane (gz a multiple of p, gy a multiple of py or equal to
+// ylast) is zeroed whole; otherwise only the rows gx = 0, p, 2p, ... are.  Threads form (row, column)
 // pairs, the columns of a row on cw = 2^cw_log2 consecutive lanes (the next
 // power of two >= ncols, at most 64), so narrow multivectors keep every lane
 // busy and wide ones store 64 contiguous columns at a time.  Rows of
 // cell-interior nodes are skipped: the box kernel writes them.
-__global__ void zero_shared_rows_kernel(double* __restrict__ Y, int Nx, int Ny, int p, int ncols,
-                                        int64_t ld, int64_t lines, int cw_log2) {
+__global__ void zero_shared_rows_kernel(double* __restrict__ Y, int Nx, int Ny, int p, int py,
+                                        int ylast, int ncols, int64_t ld, int64_t lines,
+                                        int cw_log2) {
   const int cw = 1 << cw_log2;
   const int c0 = threadIdx.x & (cw - 1);
   const int r0 = threadIdx.x >> cw_log2, rstep = blockDim.x >> cw_log2;
   for (int64_t line = blockIdx.x; line < lines; line += gridDim.x) {
     const int gy = (int)(line % Ny), gz = (int)(line / Ny);
-    const bool full = (gy % p == 0) || (gz % p == 0);
+    const bool full = (gy % py == 0) || gy == ylast || (gz % p == 0);
     const int step = full ? 1 : p;
     const int nrows = full ? Nx : (Nx + p - 1) / p;
     double* base = Y + line * Nx * ld;
@@ -220,8 +221,8 @@ int batched_blocks_per_cu(int prec, int bcfg) {
   return 0;
 }
 
-hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int ncols, int64_t ld,
-                                   hipStream_t s) {
+hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int py, int ncols,
+                                   int64_t ld, hipStream_t s) {
   const int64_t lines = nodes[1] * nodes[2];
   if (lines < 1 || ncols < 1) return hipSuccess;
   int cw_log2 = 0;
@@ -232,7 +233,8 @@ hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int
   if (wgs < 256) wgs = 256;
   if (wgs > lines) wgs = lines;
   hipLaunchKernelGGL(zero_shared_rows_kernel, dim3((unsigned)wgs), dim3(256), 0, s, Y,
-                     (int)nodes[0], (int)nodes[1], p, ncols, ld, lines, cw_log2);
+                     (int)nodes[0], (int)nodes[1], p, py,
+                     nodes[1] % p == 1 || p == 1 ? (int)nodes[1] - 1 : -1, ncols, ld, lines, cw_log2);
   return hipGetLastError();
 }
 
@@ -451,6 +453,73 @@ hipError_t launch_apply_box(const Operator& op, const ApplyLaunch& a, hipStream_
     case 8: return launch_apply_box_p<8>(op, a, s);
     case 9: return launch_apply_box_p<9>(op, a, s);
     case 10: return launch_apply_box_p<10>(op, a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+bool pair_built(int q) { return q <= 7; }
+
+// Where the register-resident apply is the built-in choice: at most seven points per
+// direction, and enough cells for its one or two wavefronts per SIMD to run
+// several each (a single cell takes a wavefront some 15 us, so on small
+// multivectors the box kernel's many short workgroups finish first).  Measured
+// at cells-times-tiles per resident wavefront: p = 6, 16^3 cells, 4 (16 columns)
+// 128 against 117 us, 8 (32) 224 against 257, 16 (64) 415 against 506; p = 4, 24^3,
+// 3.4 (8 columns) 85 against 86, 6.8 (16) 132 against 158; column counts that leave
+// part of the box kernel's tiles idle win earlier (p = 6, 12 columns, 4: 135
+// against 151); p = 2, 32^3, 2 (one column) 32 against 75.  Six points have
+// three pairs for four lane groups and do not win (p = 5, 14^3, 64 columns: 218
+// against 215 us).
+bool pair_chosen(const Operator& op, int nvec) {
+  if (op.nq > 7 || op.nq == 6) return false;
+  const int cols = pair_columns(nvec), lx = pair_cells(cols);
+  const double steps = (double)((op.grid.n[0] + lx - 1) / lx) * op.grid.n[1] * op.grid.n[2] *
+                       ((nvec + cols - 1) / cols) / (1024.0 * pair_waves(op.nq));
+  return steps >= (op.nq <= 3 ? 2.0 : nvec % 8 != 0 && nvec > 8 ? 4.0 : 6.0);
+}
+
+// The columns per wavefront and the segment length of the register-resident
+// apply.  Segments: shorter ones give more wavefronts, longer ones share more
+// rows between consecutive cells, and a wavefront's first cell has nothing to
+// hide its loads behind; the estimate is rounds of resident wavefronts times
+// (cells of a segment + that start).
+PairPlan pair_plan(const Operator& op, int nvec) {
+  PairPlan b{};
+  b.cols = pair_columns(nvec);
+  b.ntiles = (nvec + b.cols - 1) / b.cols;
+  const int lx = pair_cells(b.cols);
+  b.nxg = (op.grid.n[0] + lx - 1) / lx;
+  const int64_t lines = (int64_t)b.nxg * op.grid.n[2] * b.ntiles, ny = op.grid.n[1];
+  const double slots = 1024.0 * pair_waves(op.nq);
+  double best = 0.0;
+  for (int64_t nseg = 1; nseg <= ny; ++nseg) {
+    const int64_t len = (ny + nseg - 1) / nseg;
+    if ((ny + len - 1) / len != nseg) continue;
+    const double r = (double)(lines * nseg) / slots;
+    const double rounds = r < 4.0 ? (double)(int64_t)(r + 0.999999) : r + 0.5;
+    const double cost = rounds * ((double)len + 0.5);  // p = 6, 16^3, 64 columns: 406 us in one
+                                                       // segment of 16, 422 in two, 453 in four
+    if (b.len == 0 || cost < best) {
+      best = cost;
+      b.len = (int)len;
+      b.nseg = (int)nseg;
+    }
+  }
+  const int64_t items = lines * b.nseg;
+  b.items = items < (1LL << 30) ? (int)items : 0;
+  b.chunk = (items + 7) / 8;
+  return b;
+}
+
+hipError_t launch_apply_pair(const Operator& op, const ApplyLaunch& a, const PairPlan& plan,
+                             hipStream_t s) {
+  switch (op.p) {
+    case 1: return launch_apply_pair_p<1>(op, a, plan, s);
+    case 2: return launch_apply_pair_p<2>(op, a, plan, s);
+    case 3: return launch_apply_pair_p<3>(op, a, plan, s);
+    case 4: return launch_apply_pair_p<4>(op, a, plan, s);
+    case 5: return launch_apply_pair_p<5>(op, a, plan, s);
+    case 6: return launch_apply_pair_p<6>(op, a, plan, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -132,6 +132,13 @@ struct ApplyLaunch {
   bool accumulate;
 };
 
+// Work split of the register-resident apply (apply_pair.hip): items are
+// (segment of `len` cells along y, group of 16 / cols cells in x, cell layer z,
+// column tile), the tile fastest; chunk = items per XCD.
+struct PairPlan {
+  int cols, ntiles, nxg, nseg, len, items;
+  int64_t chunk;
+};
 // Arguments of a fused Chebyshev filter step, Out := a D A (D Y) + b Y + c Xp.
 struct ChebArgs {
   const double* D;   // M^{-1/2} per row (0 on constrained rows)
@@ -244,10 +251,19 @@ int cache_store(const char* path, const std::string& key, int cfg, const std::ve
 hipError_t launch_zero_rows(double* Y, int64_t nrows, int ncols, int64_t ld, hipStream_t s);
 // Zero the rows of nodes on cell faces (some grid index a multiple of p) of an
 // Nx x Ny x Nz node grid: the rows the box kernel assembles with atomics.
-hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int ncols, int64_t ld,
-                                   hipStream_t s);
+// py: the same with y planes only at the multiples of py (a multiple of p) and
+// at the last plane of a free direction.
+hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int py, int ncols,
+                                   int64_t ld, hipStream_t s);
 // FP64 fused apply for box cells.
 hipError_t launch_apply_box(const Operator& op, const ApplyLaunch& a, hipStream_t s);
+// Register-resident form of the same (q <= 7, spans below kPairMaxSpan bytes).
+constexpr int64_t kPairMaxSpan = 0xF0000000LL;
+bool pair_built(int q);
+bool pair_chosen(const Operator& op, int nvec);
+PairPlan pair_plan(const Operator& op, int nvec);
+hipError_t launch_apply_pair(const Operator& op, const ApplyLaunch& a, const PairPlan& plan,
+                             hipStream_t s);
 // FP64 matrix-core body (shape 10: 8 columns per item).
 hipError_t launch_apply_mfma(const Operator& op, const ApplyLaunch& a, hipStream_t s);
 bool apply_box_supported(int p, int q, int cfg);

@@ -525,6 +525,22 @@ template <int P>
 hipError_t launch_apply_mixed_p(const Operator& op, const ApplyLaunch& a, int prec, hipStream_t s);
 template <int P>
 hipError_t launch_apply_box_p(const Operator& op, const ApplyLaunch& a, hipStream_t s);
+// Wavefronts per SIMD of the register-resident body: two planes of nq^2 values
+// before and after the derivative stage, 8 nq^2 registers, and about 60 more.
+constexpr int pair_waves(int nq) {
+  const int w = 512 / (8 * nq * nq + 56);
+  return w < 1 ? 1 : (w > 4 ? 4 : w);
+}
+// Cells adjacent in x that share a wavefront's 16 column slots at B columns: at
+// most four, so that a mesh of a few thousand cells still gives every SIMD a
+// wavefront.
+constexpr int pair_cells(int B) { return B >= 16 ? 1 : B == 8 ? 2 : 4; }
+constexpr int pair_columns(int nvec) {
+  return nvec > 8 ? 16 : nvec > 4 ? 8 : nvec > 2 ? 4 : nvec;
+}
+template <int P>
+hipError_t launch_apply_pair_p(const Operator& op, const ApplyLaunch& a, const PairPlan& plan,
+                               hipStream_t s);
 template <int P>
 hipError_t launch_apply_mfma_p(const Operator& op, const ApplyLaunch& a, hipStream_t s);
 template <int P>
