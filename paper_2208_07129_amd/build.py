@@ -48,7 +48,8 @@ def jobs():
         ("blas64.hip", "blas64.o", []),
         ("eig.hip", "eig.o", []),
         ("capi_solver.cpp", "capi_solver.o", []),
-        ("mlp.hip", "mlp.o", []),
+        # matrix-core sums straight in the vector registers: four wavefronts per SIMD
+        ("mlp.hip", "mlp.o", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
         ("capi_mlp.cpp", "capi_mlp.o", []),
         ("capi_cheb.cpp", "capi_cheb.o", []),
         ("refine.cpp", "refine.o", []),

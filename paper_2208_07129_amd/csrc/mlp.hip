@@ -8,11 +8,10 @@
 // block contiguously (element (i, e k + j) at e * ld + i * k + j): the cell
 // gather and the node assembly then stream whole cells instead of 256-byte
 // pieces a batch row apart.  The GEMM runs on the gfx950 matrix cores
-// (v_mfma_f32_16x16x32_bf16: BF16 operands, FP32 accumulation): one 64 x 64
-// output tile per 256-thread workgroup, 2 x 2 waves of 32 x 32, K staged
-// through LDS in steps of 32 with k contiguous per lane, so every fragment is
-// one 16-byte LDS read.  Transposed operands (backward pass) are transposed
-// while being staged.  Epilogues fuse bias, ReLU, the ReLU mask of the
+// (v_mfma_f32_16x16x32_bf16: BF16 operands, FP32 accumulation, k in order): one
+// kernel walks down M with its columns of a long batch in registers, the other
+// takes 128 x 128 or 64 x 64 output tiles per 256-thread workgroup with K staged
+// through LDS in steps of 32.  Epilogues fuse bias, ReLU, the ReLU mask of the
 // backward pass and the BF16 conversion; weight gradients split the batch
 // dimension across workgroups and add FP32 partial tiles atomically.
 #include <cmath>
@@ -35,131 +34,514 @@ __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32
 
 namespace {
 
-constexpr int kTile = 64, kKStep = 32, kPad = 40;  // LDS rows of 80 bytes
+constexpr int kKStep = 32, kPad = 40;  // LDS rows of 80 bytes
 
 // C (M x N) = op(A) (M x K) * op(B) (K x N).  A: row-major M x K (lda), or,
 // with TA, stored K x M.  B: row-major K x N (ldb), or, with TB, stored N x K.
-// M, N, K multiples of 8 (8-element, 16-byte staging chunks).  blockIdx.z
-// takes the K range [z kchunk, (z+1) kchunk).  Output tiles are numbered with
-// the M tile fastest, and workgroup b takes tile (b mod 8) c + b / 8 (c =
-// gridDim.x / 8): consecutive workgroups go to different XCDs, so this gives
-// each XCD a contiguous range of tiles and the few tiles that share an N slice
-// of B (the long batch operand) run on one XCD, which reads that slice from
-// HBM once into its L2.
-template <bool TA, bool TB>
+// M, N, K multiples of 8.  The K range is cut into pieces of kchunk.  Output
+// tiles (T x T) are numbered with the M tile fastest, then N, then the K piece,
+// and workgroup b takes tile (b mod 8) c + b / 8 (c = gridDim.x / 8):
+// consecutive workgroups go to different XCDs, so this gives each XCD a
+// contiguous range of tiles, and the tiles that share an N slice of B (the long
+// batch operand), or a K piece of both operands, run on one XCD, which reads
+// them from HBM once into its L2.
+//
+// 2 x 2 wavefronts of T/2 x T/2.  What bounds it is LDS and staging work per
+// matrix instruction, so T = 128 (16 matrix instructions per 8 fragment reads;
+// T = 64: 4 per 4) wherever the tiles fill the chip.  Two wavefronts stage A,
+// two stage B.  An operand stored with k running slowest is transposed in
+// registers: a thread loads 8 k rows of T/32 columns and permutes them to
+// 16-byte runs of k (one byte permute per two elements; storing single elements
+// into LDS took eight stores a chunk).  Run c of LDS row r sits at place
+// c ^ (r / 16 mod 4): with 80-byte rows neither those stores nor the fragment
+// reads meet on a bank.  Without TB the matrix instruction takes B as its first
+// operand, so a lane holds four consecutive columns of C and stores 16 bytes.
+//
+// 344 x 600 x 128000 (TB, split K): 146 us, 361 TFLOP/s (64 x 64 tiles with
+// element-wise transposing stores and loads selected after they arrive: 250).
+struct GemmVec {  // whether the tiled kernel's outputs take 4-element stores and its mask 4-element loads
+  int f32, bf16, mask;
+};
+
+// Staging of one operand: T rows (of m or n) by 32 k, by 128 threads.  Loads go
+// through a buffer whose base moves by a step's k (uniform 64-bit address) with
+// 32-bit offsets per lane; what lies outside the operand takes an offset past
+// the buffer's end and reads 0 (a select on the loaded value would have to wait
+// for it).  FAR: the offsets of one step exceed 32 bits; addresses are formed in
+// 64 bits and the values selected.
+constexpr uint32_t kGemmBuffer = 0xFFFF0000u;  // bytes; also the offset that reads 0
+template <int T, bool TR, bool FAR>
+struct GemmStage {
+  static constexpr int NV = T / 32;  // columns per thread (TR), row passes otherwise
+  const uint16_t* base;  // uniform: element (first row or column of the tile, k = kb)
+  int64_t kstep;         // elements from one step's base to the next
+  int64_t rs;            // TR: stride of k rows; otherwise of 32 rows
+  uint32_t off[TR ? 1 : NV];
+  int64_t far;           // FAR: this thread's first element from base
+  int kk, row;           // first k of this thread in a step, first row or column
+  int left;              // rows or columns of the operand from this thread's first on
+};
+
+// Thread u's part of the rows [r0, r0 + T) of R from k = kb on (TR, blk > 0:
+// columns in blocks of blk, ld the block stride, k rows blk apart).
+template <int T, bool TR, bool FAR>
+__device__ __forceinline__ GemmStage<T, TR, FAR> gemm_stage(const uint16_t* X, int64_t ld, int r0,
+                                                            int R, int kb, int blk, int u) {
+  GemmStage<T, TR, FAR> s;
+  s.kk = TR ? (u >> 5) * 8 : (u & 3) * 8;
+  s.row = TR ? (u & 31) * s.NV : u >> 2;
+  s.left = R - r0 - s.row;
+  if constexpr (TR) {
+    s.rs = blk > 0 ? blk : ld;
+    s.kstep = kKStep * s.rs;
+    const int b0 = blk > 0 ? r0 / blk : 0, r = s.left > 0 ? r0 + s.row : r0;
+    s.base = X + (blk > 0 ? (int64_t)b0 * ld : r0) + kb * s.rs;
+    s.far = blk > 0 ? (int64_t)(r / blk - b0) * ld + r % blk : r - r0;
+    s.off[0] = s.left > 0 ? (uint32_t)(2 * (s.far + s.kk * s.rs)) : kGemmBuffer;
+  } else {
+    s.rs = 32 * ld;
+    s.kstep = kKStep;
+    s.base = X + (int64_t)r0 * ld + kb;
+    s.far = s.left > 0 ? s.row * ld : 0;
+#pragma unroll
+    for (int i = 0; i < s.NV; ++i)
+      s.off[i] = 32 * i < s.left ? (uint32_t)(2 * ((s.row + 32 * i) * ld + s.kk)) : kGemmBuffer;
+  }
+  return s;
+}
+
+// The step's loads (step: its number, rem: how many of its 32 k there are).
+template <int T, bool TR, bool FAR>
+__device__ __forceinline__ void gemm_load(const GemmStage<T, TR, FAR>& s, uint32_t* v, int step,
+                                          int rem) {
+  constexpr int NV = T / 32;
+  const bool kin = s.kk < rem;
+  const uint16_t* base = s.base + step * s.kstep;
+  if constexpr (FAR) {
+    if constexpr (TR) {
+      const bool in = kin && s.left > 0;
+      const uint16_t* q = base + s.far + (kin ? s.kk * s.rs : 0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int n = 0; n < NV / 2; ++n) {
+          const uint32_t x = *reinterpret_cast<const uint32_t*>(q + i * s.rs + 2 * n);
+          v[i * (NV / 2) + n] = in ? x : 0u;
+        }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const bool in = kin && 32 * i < s.left;
+        const uint4 x = *reinterpret_cast<const uint4*>(base + s.far + (kin ? s.kk : 0) +
+                                                        (in ? i * s.rs : 0));
+        v[4 * i] = in ? x.x : 0u;
+        v[4 * i + 1] = in ? x.y : 0u;
+        v[4 * i + 2] = in ? x.z : 0u;
+        v[4 * i + 3] = in ? x.w : 0u;
+      }
+    }
+  } else {
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0,
+                                                        (int)kGemmBuffer, 0x00020000);
+    if constexpr (TR) {
+      const int o = kin ? (int)s.off[0] : (int)kGemmBuffer;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int so = (int)(2 * i * s.rs);
+        if constexpr (NV == 4) {
+          const auto x = __builtin_amdgcn_raw_buffer_load_b64(rsrc, o, so, 0);
+          v[2 * i] = x[0];
+          v[2 * i + 1] = x[1];
+        } else {
+          v[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, o, so, 0);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int o = kin ? (int)s.off[i] : (int)kGemmBuffer;
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v[4 * i + w] = x[w];
+      }
+    }
+  }
+}
+
+template <int T, bool TR, bool FAR>
+__device__ __forceinline__ void gemm_store(const GemmStage<T, TR, FAR>& s, const uint32_t* v,
+                                           uint16_t (*sh)[kPad]) {
+  constexpr int NV = T / 32;
+  auto put = [&](int r, uint4 x) {
+    *reinterpret_cast<uint4*>(&sh[r][((s.kk >> 3) ^ ((r >> 4) & 3)) * 8]) = x;
+  };
+#pragma unroll
+  for (int n = 0; n < NV; ++n) {
+    if constexpr (TR) {
+      const uint32_t sel = n & 1 ? 0x07060302u : 0x05040100u;
+      uint32_t w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        w[i] = __builtin_amdgcn_perm(v[(2 * i + 1) * (NV / 2) + n / 2],
+                                     v[(2 * i) * (NV / 2) + n / 2], sel);
+      put(s.row + n, uint4{w[0], w[1], w[2], w[3]});
+    } else {
+      put(s.row + 32 * n, uint4{v[4 * n], v[4 * n + 1], v[4 * n + 2], v[4 * n + 3]});
+    }
+  }
+}
+
+template <int T, bool TA, bool TB, bool FAR>
 __global__ void __launch_bounds__(256)
 gemm_bf16_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
-                 const uint16_t* __restrict__ B, int64_t ldb, int kchunk, GemmEpi ep) {
+                 const uint16_t* __restrict__ B, int64_t ldb, int kchunk, GemmEpi ep,
+                 GemmVec vec) {
   // two LDS buffers: step s is staged into buffer s mod 2 while its global
   // loads for step s + 1 are already in flight (one barrier per step)
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][kTile][kPad];  // [m][k]
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kTile][kPad];  // [n][k]
-  const int mtiles = (M + kTile - 1) / kTile;
-  const int64_t tiles = (int64_t)mtiles * ((N + kTile - 1) / kTile);
+  __shared__ __attribute__((aligned(16))) uint16_t As[2][T][kPad];  // [m][k]
+  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][T][kPad];  // [n][k]
+  constexpr int W = T / 32;  // 16 x 16 tiles per direction of a wavefront
+  const int mtiles = (M + T - 1) / T, ntiles = (N + T - 1) / T;
+  const int64_t tiles = (int64_t)mtiles * ntiles;
   const int64_t lt = (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
-  if (lt >= tiles) return;  // the few padding workgroups of the last XCD range
-  const int m0 = (int)(lt % mtiles) * kTile, n0 = (int)(lt / mtiles) * kTile;
-  const int kb = blockIdx.z * kchunk;
+  const int kz = (K + kchunk - 1) / kchunk;
+  if (lt >= tiles * kz) return;  // the few padding workgroups of the last XCD range
+  const int64_t mn = lt % tiles;
+  const int m0 = (int)(mn % mtiles) * T, n0 = (int)(mn / mtiles) * T;
+  const int kb = (int)(lt / tiles) * kchunk;
   const int ke = min(K, kb + kchunk);
-  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  f32x4 acc[2][2];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = (wave >> 1) * (T / 2), wn = (wave & 1) * (T / 2);
+  f32x4 acc[W][W];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < W; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < W; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // This thread's 16-byte staging chunk of each operand.  A transposed operand
-  // is transposed while stored (eight 2-byte stores); the lanes of a
-  // wavefront then span the 32 k rows, so those stores fall on 32 banks.
-  // Loads read clamped (valid) addresses and a select zeroes what lies
-  // outside the operand, so no load sits behind a branch.
-  const uint4 zero = {0u, 0u, 0u, 0u};
-  const int a_kk = TA ? (t & 31) : (t & 3) * 8, a_m = TA ? (t >> 5) * 8 : (t >> 2);
-  const int b_kk = TB ? (t & 3) * 8 : (t & 31), b_n = TB ? (t >> 2) : (t >> 5) * 8;
-  uint4 va, vb;
-  auto gload = [&](int k0) {
-    {
-      const int kk = k0 + a_kk, m = m0 + a_m;
-      const bool ok = kk < ke && m < M;
-      const int kc = ok ? kk : kb, mc = ok ? m : m0;
-      const uint4 v = TA ? *reinterpret_cast<const uint4*>(A + (int64_t)kc * lda + mc)
-                         : *reinterpret_cast<const uint4*>(A + (int64_t)mc * lda + kc);
-      va = ok ? v : zero;
-    }
-    {
-      const int kk = k0 + b_kk, nn = n0 + b_n;
-      const bool ok = kk < ke && nn < N;
-      const int kc = ok ? kk : kb, nc = ok ? nn : n0;
-      int64_t off;
-      if constexpr (TB) off = (int64_t)nc * ldb + kc;
-      else  // 8 columns inside one block (kb multiple of 8)
-        off = ep.kb > 0 ? (int64_t)(nc / ep.kb) * ldb + (int64_t)kc * ep.kb + nc % ep.kb
-                        : (int64_t)kc * ldb + nc;
-      const uint4 v = *reinterpret_cast<const uint4*>(B + off);
-      vb = ok ? v : zero;
-    }
-  };
-  auto lstore = [&](int buf) {
-    if constexpr (TA) {
-      const uint16_t* e = reinterpret_cast<const uint16_t*>(&va);
+  auto product = [&](int buf) {
+    bf16x8 a[W], b[W];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) As[buf][a_m + i][a_kk] = e[i];
-    } else {
-      *reinterpret_cast<uint4*>(&As[buf][a_m][a_kk]) = va;
+    for (int i = 0; i < W; ++i) {
+      const int ra = wm + i * 16 + (lane & 15), rb = wn + i * 16 + (lane & 15);
+      a[i] = *reinterpret_cast<const bf16x8*>(&As[buf][ra][((lane >> 4) ^ ((ra >> 4) & 3)) * 8]);
+      b[i] = *reinterpret_cast<const bf16x8*>(&Bs[buf][rb][((lane >> 4) ^ ((rb >> 4) & 3)) * 8]);
     }
-    if constexpr (TB) {
-      *reinterpret_cast<uint4*>(&Bs[buf][b_n][b_kk]) = vb;
-    } else {
-      const uint16_t* e = reinterpret_cast<const uint16_t*>(&vb);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) Bs[buf][b_n + i][b_kk] = e[i];
-    }
+    for (int i = 0; i < W; ++i)
+#pragma unroll
+      for (int j = 0; j < W; ++j)
+        acc[i][j] = TB ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
   };
-  gload(kb);
-  for (int k0 = kb, step = 0; k0 < ke; k0 += kKStep, ++step) {
-    const int buf = step & 1;
-    lstore(buf);
+  const bool on_a = wave < 2;
+  const auto sa = gemm_stage<T, TA, FAR>(A, lda, m0, M, kb, 0, t & 127);
+  const auto sb = gemm_stage<T, !TB, FAR>(B, ldb, n0, N, kb, ep.kb, t & 127);
+  uint32_t v[2][T / 8];  // the next two steps' operands
+  const int nsteps = (ke - kb + kKStep - 1) / kKStep;
+  auto load = [&](int step, uint32_t* w) {
+    const int rem = ke - kb - step * kKStep;
+    if (on_a) gemm_load(sa, w, step, rem);
+    else gemm_load(sb, w, step, rem);
+  };
+  auto one = [&](int step, int buf) {
+    if (on_a) gemm_store(sa, v[buf], As[buf]);
+    else gemm_store(sb, v[buf], Bs[buf]);
     __syncthreads();
-    if (k0 + kKStep < ke) gload(k0 + kKStep);
-    bf16x8 a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      a[i] = *reinterpret_cast<const bf16x8*>(&As[buf][wm + i * 16 + (lane & 15)][(lane >> 4) * 8]);
-      b[i] = *reinterpret_cast<const bf16x8*>(&Bs[buf][wn + i * 16 + (lane & 15)][(lane >> 4) * 8]);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    if (step + 2 < nsteps) load(step + 2, v[buf]);
+    product(buf);
+  };
+  load(0, v[0]);
+  if (nsteps > 1) load(1, v[1]);
+  for (int step = 0; step < nsteps; step += 2) {
+    one(step, 0);
+    if (step + 1 < nsteps) one(step + 1, 1);
   }
 
-  // D layout of the 16 x 16 tile: lane -> column lane % 16, rows 4 (lane / 16) + r
+  // D layout of the 16 x 16 tile: lane -> column lane % 16, rows 4 (lane / 16) + r;
+  // rows are m with TB, n otherwise
+  auto post = [&](float v, float bias) {
+    if (ep.bias) v += bias;
+    if (ep.relu) v = v > 0.f ? v : 0.f;
+    return v;
+  };
+  if constexpr (TB) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < W; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < W; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
+          const int n = n0 + wn + j * 16 + (lane & 15);
+          if (m >= M || n >= N) continue;
+          float x = post(acc[i][j][r], ep.bias ? ep.bias[m] : 0.f);
+          if (ep.mask && !(bf16_to_f32(ep.mask[(int64_t)m * ep.ldmask + n]) > 0.f)) x = 0.f;
+          if (ep.out_f32) {
+            float* o = ep.out_f32 + (int64_t)m * ep.ld_f32 + n;
+            if (ep.atomic) unsafeAtomicAdd(o, x);
+            else *o = x;
+          }
+          if (ep.out_bf16) ep.out_bf16[(int64_t)m * ep.ld_bf16 + n] = f32_to_bf16(x);
+        }
+  } else {
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      const int n = n0 + wn + j * 16 + (lane >> 4) * 4;  // four columns, inside one block
+      if (n >= N) continue;
+      const int64_t nb = ep.kb > 0 ? n / ep.kb : 0, nr = ep.kb > 0 ? n % ep.kb : n;
+      const int64_t of = ep.kb > 0 ? nb * ep.ld_f32 + nr : nr, sf = ep.kb > 0 ? ep.kb : ep.ld_f32;
+      const int64_t ob = ep.kb > 0 ? nb * ep.ld_bf16 + nr : nr,
+                    sb = ep.kb > 0 ? ep.kb : ep.ld_bf16;
+#pragma unroll
+      for (int i = 0; i < W; ++i) {
+        const int m = m0 + wm + i * 16 + (lane & 15);
+        if (m >= M) continue;
+        const float bias = ep.bias ? ep.bias[m] : 0.f;
+        f32x4 x;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = post(acc[i][j][r], bias);
+        if (ep.mask) {
+          const uint16_t* q = ep.mask + (int64_t)m * ep.ldmask + n;
+          ushort4 h;
+          if (vec.mask) h = *reinterpret_cast<const ushort4*>(q);
+          else h = ushort4{q[0], q[1], q[2], q[3]};
+          if (!(bf16_to_f32(h.x) > 0.f)) x[0] = 0.f;
+          if (!(bf16_to_f32(h.y) > 0.f)) x[1] = 0.f;
+          if (!(bf16_to_f32(h.z) > 0.f)) x[2] = 0.f;
+          if (!(bf16_to_f32(h.w) > 0.f)) x[3] = 0.f;
+        }
+        if (ep.out_f32) {
+          float* o = ep.out_f32 + of + m * sf;
+          if (ep.atomic) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) unsafeAtomicAdd(o + r, x[r]);
+          } else if (vec.f32) {
+            *reinterpret_cast<f32x4*>(o) = x;
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = x[r];
+          }
+        }
+        if (ep.out_bf16) {
+          uint16_t* o = ep.out_bf16 + ob + m * sb;
+          const ushort4 h{f32_to_bf16(x[0]), f32_to_bf16(x[1]), f32_to_bf16(x[2]),
+                          f32_to_bf16(x[3])};
+          if (vec.bf16) {
+            *reinterpret_cast<ushort4*>(o) = h;
+          } else {
+            o[0] = h.x;
+            o[1] = h.y;
+            o[2] = h.z;
+            o[3] = h.w;
+          }
+        }
+      }
+    }
+  }
+}
+
+// The same product for op(B) = B (a long batch N), K <= 32 KS and no split.  A
+// wavefront keeps its 16 NB columns of B in registers for the whole K range and
+// the workgroup walks down M, 16 rows at a time, so B is read from memory once
+// (the tiled kernel reads it once per 128 rows of C) and only A (the weights)
+// goes through LDS, laid out as the matrix instruction's operands (every LDS
+// access is contiguous), two steps deep.  A lane loads NB neighbouring columns
+// of 8 k rows of B and permutes them to runs of k, which leaves it with columns
+// NB c .. NB c + NB - 1 of C (c = lane % 16): one store per row, 64 NB bytes of
+// FP32 in a run.  Bound by memory; 344 x 1024000 x 344, FP32 out, cell-blocked
+// (2.1 GB): 500 us, 4.2 TB/s; the tiled kernel below takes 980.
+// 256 x 128000 x 344, bias, ReLU, BF16 out: 45 us (72 tiled).
+// The epilogue is a template parameter and its stores are dropped past the edge
+// by the buffer's bound: with a branch the count of stores in flight is unknown
+// and every step waited for the last one's (2.3 us a step).
+constexpr int kWideMaxM = 4096;  // rows of C, for the bias in LDS
+constexpr int wide_buffer(int ks, bool ta) { return ta ? 1024 : (ks * 64 + 255) / 256 * 256; }
+enum WideEpi { kWideF32, kWideF32Bias, kWideReluBf16, kWideMaskBf16 };
+template <int KS, int NB, bool TA, int EPI>
+__global__ void __launch_bounds__(256, 2)
+gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
+                 const uint16_t* __restrict__ B, int64_t ldb, GemmEpi ep) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  constexpr int kOob = (int)kGemmBuffer;
+  extern __shared__ __attribute__((aligned(16))) char wide_sh[];
+  constexpr int kBuf = wide_buffer(KS, TA);
+  u32x4* sa = reinterpret_cast<u32x4*>(wide_sh);       // [2][KS][64], padded to kBuf
+  float* sbias = reinterpret_cast<float*>(sa + 2 * kBuf);  // [M rounded up to 16]
+  const int t = threadIdx.x, lane = t & 63, c = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int64_t lt = (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+  if (lt * 64 * NB >= N) return;
+  const int64_t n0 = (lt * 4 + wave) * (16 * NB);
+  const int64_t n = n0 + NB * c;
+  const bool nok = n < N;
+  auto rsrc_of = [](const uint16_t* p) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, kOob, 0x00020000);
+  };
+  // 8 k rows (rs2 bytes apart) of W neighbouring elements, and their W runs of k
+  auto columns = [](auto rsrc, int o, int rs2, auto wc, uint32_t* v) {
+    constexpr int W = decltype(wc)::value;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (W == 4) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b64(rsrc, o, i * rs2, 0);
+        v[2 * i] = x[0];
+        v[2 * i + 1] = x[1];
+      } else {
+        v[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, o, i * rs2, 0);
+      }
+    }
+  };
+  auto runs = [](const uint32_t* v, auto wc, u32x4* out) {
+    constexpr int W = decltype(wc)::value;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const uint32_t sel = w & 1 ? 0x07060302u : 0x05040100u;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        out[w][i] = __builtin_amdgcn_perm(v[(2 * i + 1) * (W / 2) + w / 2],
+                                          v[2 * i * (W / 2) + w / 2], sel);
+    }
+  };
+  using WB = std::integral_constant<int, NB>;
+  using W4 = std::integral_constant<int, 4>;
+  u32x4 b[KS][NB];
+  {
+    const int64_t rs = ep.kb > 0 ? ep.kb : ldb;
+    const int64_t nc = n0 < N ? n0 : 0;  // past the end: nothing is read
+    const int64_t b0 = ep.kb > 0 ? nc / ep.kb : 0;
+    const uint16_t* base = B + (ep.kb > 0 ? b0 * ldb : nc);
+    const int64_t far = ep.kb > 0 ? (n / ep.kb - b0) * ldb + n % ep.kb : n - nc;
+    const int vo = nok ? (int)(uint32_t)(2 * (far + 8 * g * rs)) : kOob;
+    uint32_t v[KS][4 * NB];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      columns(rsrc_of(base + ks * 32 * rs), 32 * ks + 8 * g < K ? vo : kOob, (int)(2 * rs), WB{},
+              v[ks]);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) runs(v[ks], WB{}, b[ks]);
+  }
+  // staging of 16 rows of A: TA one item (8 k rows, 4 columns) per thread,
+  // otherwise PT runs of 8 k; the operand of (ks, g, row r) at sa[ks][16 g + r]
+  constexpr int PT = TA ? 1 : (KS * 64 + 255) / 256;
+  static_assert(!TA || KS * 16 <= 256, "one item per thread");
+  uint32_t st[TA ? 16 : 4 * PT];
+  auto stage_load = [&](int m0) {
+    if constexpr (TA) {
+      const int m = m0 + (t & 3) * 4, k = (t >> 2) * 8;
+      const int o = m < M && k < K ? (int)(uint32_t)(2 * (k * lda + m)) : kOob;
+      columns(rsrc_of(A), o, (int)(2 * lda), W4{}, st);
+    } else {
+#pragma unroll
+      for (int i = 0; i < PT; ++i) {
+        const int e = t + 256 * i, m = m0 + (e & 15), k = (e >> 4) * 8;
+        const int o = m < M && k < K ? (int)(uint32_t)(2 * ((e & 15) * lda + k)) : kOob;
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(A + (int64_t)m0 * lda), o, 0, 0);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) st[4 * i + w] = x[w];
+      }
+    }
+  };
+  auto stage_store = [&](u32x4* dst) {
+    if constexpr (TA) {
+      u32x4 x[4];
+      runs(st, W4{}, x);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) dst[(t >> 2) * 16 + (t & 3) * 4 + j] = x[j];
+    } else {
+#pragma unroll
+      for (int i = 0; i < PT; ++i)
+        dst[t + 256 * i] = u32x4{st[4 * i], st[4 * i + 1], st[4 * i + 2], st[4 * i + 3]};
+    }
+  };
+  // this lane's place in C (rows 4 g .. 4 g + 3 of a step) and the mask, in bytes
+  // from a uniform base that moves 16 rows a step
+  constexpr bool kF32 = EPI == kWideF32 || EPI == kWideF32Bias;
+  constexpr int SZ = kF32 ? 4 : 2;
+  const int64_t ldc = kF32 ? ep.ld_f32 : ep.ld_bf16;
+  const int64_t sc = ep.kb > 0 ? ep.kb : ldc;
+  const int64_t nc = n0 < N ? n0 : 0, b0 = ep.kb > 0 ? nc / ep.kb : 0;
+  char* cbase = (kF32 ? reinterpret_cast<char*>(ep.out_f32) : reinterpret_cast<char*>(ep.out_bf16)) +
+                SZ * (ep.kb > 0 ? b0 * ldc : nc);
+  const int co = nok ? (int)(uint32_t)(SZ * ((ep.kb > 0 ? (n / ep.kb - b0) * ldc + n % ep.kb
+                                                        : n - nc) + 4 * g * sc))
+                     : kOob;
+  const uint16_t* mbase = EPI == kWideMaskBf16 ? ep.mask + nc : nullptr;
+  const int mo = nok ? (int)(uint32_t)(2 * (n - nc + 4 * g * ep.ldmask)) : kOob;
+  stage_load(0);
+  if constexpr (EPI == kWideF32Bias || EPI == kWideReluBf16)
+    for (int i = t; i < (M + 15) / 16 * 16; i += 256) sbias[i] = ep.bias && i < M ? ep.bias[i] : 0.f;
+  stage_store(sa);
+  stage_load(16);
+  __syncthreads();
+  for (int m0 = 0, buf = 0; m0 < M; m0 += 16, buf ^= 1) {
+    stage_store(sa + (buf ^ 1) * kBuf);
+    stage_load(m0 + 32);
+    const bool in = m0 + 4 * g < M;  // M is a multiple of 8
+    uint32_t hm[4][NB / 2];
+    if constexpr (EPI == kWideMaskBf16) {
+      const auto rm = rsrc_of(mbase + (int64_t)m0 * ep.ldmask);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
-        const int n = n0 + wn + j * 16 + (lane & 15);
-        if (m >= M || n >= N) continue;
-        float v = acc[i][j][r];
-        if (ep.bias) v += ep.bias[m];
-        if (ep.relu) v = v > 0.f ? v : 0.f;
-        if (ep.mask && !(bf16_to_f32(ep.mask[(int64_t)m * ep.ldmask + n]) > 0.f)) v = 0.f;
-        const int64_t nb = ep.kb > 0 ? (int64_t)(n / ep.kb) : 0, nr = ep.kb > 0 ? n % ep.kb : n;
-        if (ep.out_f32) {
-          float* o = ep.out_f32 + (ep.kb > 0 ? nb * ep.ld_f32 + (int64_t)m * ep.kb + nr
-                                             : (int64_t)m * ep.ld_f32 + n);
-          if (ep.atomic) unsafeAtomicAdd(o, v);
-          else *o = v;
+        if constexpr (NB == 4) {
+          const auto d = __builtin_amdgcn_raw_buffer_load_b64(rm, in ? mo : kOob,
+                                                              (int)(2 * r * ep.ldmask), 0);
+          hm[r][0] = d[0];
+          hm[r][1] = d[1];
+        } else {
+          hm[r][0] = __builtin_amdgcn_raw_buffer_load_b32(rm, in ? mo : kOob,
+                                                          (int)(2 * r * ep.ldmask), 0);
         }
-        if (ep.out_bf16)
-          ep.out_bf16[ep.kb > 0 ? nb * ep.ld_bf16 + (int64_t)m * ep.kb + nr
-                                : (int64_t)m * ep.ld_bf16 + n] = f32_to_bf16(v);
       }
+    }
+    f32x4 acc[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const u32x4* a = sa + buf * kBuf + lane;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 x = __builtin_bit_cast(bf16x8, a[ks * 64]);
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, __builtin_bit_cast(bf16x8, b[ks][j]),
+                                                         acc[j], 0, 0, 0);
+    }
+    f32x4 bias;
+    if constexpr (EPI == kWideF32Bias || EPI == kWideReluBf16)
+      bias = *reinterpret_cast<const f32x4*>(&sbias[m0 + 4 * g]);
+    const auto rc =
+        __builtin_amdgcn_make_buffer_rsrc(cbase + (int64_t)SZ * m0 * sc, 0, kOob, 0x00020000);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float x[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        x[j] = acc[j][r];
+        if constexpr (EPI == kWideF32Bias || EPI == kWideReluBf16) x[j] += bias[r];
+        if constexpr (EPI == kWideReluBf16) x[j] = x[j] > 0.f ? x[j] : 0.f;
+        if constexpr (EPI == kWideMaskBf16)
+          x[j] = bf16_to_f32((uint16_t)(hm[r][j / 2] >> (16 * (j & 1)))) > 0.f ? x[j] : 0.f;
+      }
+      uint32_t d[kF32 ? NB : NB / 2];
+      if constexpr (kF32) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) d[j] = __float_as_uint(x[j]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < NB / 2; ++j)
+          d[j] = f32_to_bf16(x[2 * j]) | (uint32_t)f32_to_bf16(x[2 * j + 1]) << 16;
+      }
+      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+      const int o = in ? co : kOob, so = (int)(SZ * r * sc);
+      if constexpr (sizeof(d) == 16)
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[0], d[1], d[2], d[3]}, rc, o, so, 0);
+      else if constexpr (sizeof(d) == 8)
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{d[0], d[1]}, rc, o, so, 0);
+      else
+        __builtin_amdgcn_raw_buffer_store_b32(d[0], rc, o, so, 0);
+    }
+    __syncthreads();
+  }
 }
 
 // Partition-of-unity weight of a free node: 1 / (number of (cell, local
@@ -626,19 +1008,96 @@ unsigned blocks_for(int64_t total) {
 hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_t* A, int64_t lda,
                             const uint16_t* B, int64_t ldb, int kchunk, const GemmEpi& ep,
                             hipStream_t s) {
+  const bool split = kchunk > 0;
   if (kchunk <= 0 || kchunk > K) kchunk = K;
   kchunk = (kchunk + kKStep - 1) / kKStep * kKStep;
-  const int kz = (K + kchunk - 1) / kchunk;
-  const int64_t tiles = ((int64_t)N + kTile - 1) / kTile * ((M + kTile - 1) / kTile);
-  dim3 grid((unsigned)((tiles + kXcds - 1) / kXcds * kXcds), 1, kz);
-  if (!ta && !tb)
-    hipLaunchKernelGGL((gemm_bf16_kernel<false, false>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, kchunk, ep);
-  else if (ta && !tb)
-    hipLaunchKernelGGL((gemm_bf16_kernel<true, false>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, kchunk, ep);
-  else if (!ta && tb)
-    hipLaunchKernelGGL((gemm_bf16_kernel<false, true>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, kchunk, ep);
-  else
-    hipLaunchKernelGGL((gemm_bf16_kernel<true, true>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, kchunk, ep);
+  int kz = (K + kchunk - 1) / kchunk;
+  auto tiles_of = [&](int t) { return ((int64_t)N + t - 1) / t * (((int64_t)M + t - 1) / t); };
+  // Tiles of 128 once they give every CU two workgroups, tiles of 64 below that
+  // (344 x 8000 x 344: 20 us with 64, 22 with 128; 31000 columns: 38 and 33; 344 x
+  // 600 x 128000 in pieces: 181 and 148).  A split K range may be cut further to get there, in pieces of
+  // at least 1024: each piece adds its tile once more.
+  constexpr int kWideMinN = 32768;  // 128 columns on each of 256 CUs
+  constexpr int kFill = 512, kMinPiece = 1024;
+  if (split && tiles_of(128) * kz < kFill && K > kMinPiece) {
+    const int64_t want = (kFill + tiles_of(128) - 1) / tiles_of(128);
+    int64_t piece = (K + want - 1) / want;
+    if (piece < kMinPiece) piece = kMinPiece;
+    if (piece < kchunk) kchunk = (int)((piece + kKStep - 1) / kKStep * kKStep);
+    kz = (K + kchunk - 1) / kchunk;
+  }
+  // the 32-bit offsets of a step: T rows of an operand with k along the rows, 32
+  // k rows otherwise (in blocks: 32 rows of a block and the tile's later blocks)
+  const int64_t span_a = (ta ? 32 : 128) * lda;
+  const int64_t span_b = tb ? 128 * ldb
+                            : ep.kb > 0 ? (int64_t)32 * ep.kb + (128 / ep.kb + 1) * ldb : 32 * ldb;
+  const bool far = 2 * (span_a > span_b ? span_a : span_b) + 1024 >= (int64_t)1 << 31;
+  const bool big = !far && tiles_of(128) * kz >= kFill;
+  const int64_t total = tiles_of(big ? 128 : 64) * kz;
+  const dim3 grid((unsigned)((total + kXcds - 1) / kXcds * kXcds));
+  auto al = [](const void* p, int64_t ld, int kb, size_t n) {
+    return reinterpret_cast<uintptr_t>(p) % n == 0 && (ld % 4 == 0) && kb % 4 == 0;
+  };
+  const GemmVec vec{al(ep.out_f32, ep.ld_f32, ep.kb, 16), al(ep.out_bf16, ep.ld_bf16, ep.kb, 8),
+                    al(ep.mask, ep.ldmask, 0, 8)};
+  // A long batch takes the one-pass kernel, with 128 columns per workgroup as soon
+  // as that gives every CU one (256 x 32768 x 344: 26 us, tiled 30; 16384 columns:
+  // 22.6 and 21.8), with 256 from twice as many on (128000 columns: 45 us, 48 with
+  // 128; 65536: 35 and 34).
+  const int64_t kbn = ep.kb > 0 ? 256 / ep.kb + 1 : 0;  // blocks that a wavefront may touch
+  const int64_t ldc = ep.out_f32 ? ep.ld_f32 : ep.ld_bf16;
+  const int64_t far_wide = 4 * (16 * (ep.kb > 0 ? ep.kb : ldc) + kbn * (ldc + ldb) + 256 +
+                                (ta ? (int64_t)K : 16) * lda + K + M + 16 * ep.ldmask);
+  const int epi = ta ? (ep.mask && !ep.bias && !ep.relu && ep.out_bf16 && vec.mask ? kWideMaskBf16 : -1)
+                  : ep.mask ? -1
+                  : ep.relu ? (ep.out_bf16 ? kWideReluBf16 : -1)
+                  : ep.out_f32 ? (ep.bias ? kWideF32Bias : kWideF32) : -1;
+  const bool one_out = ep.out_f32 ? !ep.out_bf16 && vec.f32 : vec.bf16;
+  if (!tb && !ep.atomic && !far && far_wide < (int64_t)1 << 31 && epi >= 0 && one_out &&
+      M <= kWideMaxM && K <= (ta ? 352 : 608) && N >= kWideMinN) {
+    auto wide = [&](auto ksc, auto nbc, auto tac) {
+      constexpr int KS = decltype(ksc)::value, NB = decltype(nbc)::value;
+      constexpr bool TA = decltype(tac)::value;
+      const int64_t wgs = ((int64_t)N + 64 * NB - 1) / (64 * NB);
+      const dim3 wgrid((unsigned)((wgs + kXcds - 1) / kXcds * kXcds));
+      const size_t lds = 2 * 16 * wide_buffer(KS, TA) + ((size_t)M + 15) / 16 * 64;  // <= 56 KiB
+      auto run = [&](auto ec) {
+        hipLaunchKernelGGL((gemm_wide_kernel<KS, NB, TA, decltype(ec)::value>), wgrid, dim3(256),
+                           lds, s, M, N, K, A, lda, B, ldb, ep);
+      };
+      if constexpr (TA) run(std::integral_constant<int, kWideMaskBf16>{});
+      else if (epi == kWideF32) run(std::integral_constant<int, kWideF32>{});
+      else if (epi == kWideF32Bias) run(std::integral_constant<int, kWideF32Bias>{});
+      else run(std::integral_constant<int, kWideReluBf16>{});
+    };
+    auto by_k = [&](auto nbc, auto tac) {
+      if (K <= 128) wide(std::integral_constant<int, 4>{}, nbc, tac);
+      else if (K <= 256) wide(std::integral_constant<int, 8>{}, nbc, tac);
+      else wide(std::integral_constant<int, 11>{}, nbc, tac);
+    };
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    if (K > 352) wide(std::integral_constant<int, 19>{}, I2{}, std::false_type{});
+    else if (ta && N >= 2 * kWideMinN) by_k(I4{}, std::true_type{});
+    else if (ta) by_k(I2{}, std::true_type{});
+    else if (N >= 2 * kWideMinN) by_k(I4{}, std::false_type{});
+    else by_k(I2{}, std::false_type{});
+    return hipGetLastError();
+  }
+  auto go = [&](auto tc, auto fa, auto fb, auto fr) {
+    hipLaunchKernelGGL((gemm_bf16_kernel<decltype(tc)::value, decltype(fa)::value,
+                                         decltype(fb)::value, decltype(fr)::value>),
+                       grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, kchunk, ep, vec);
+  };
+  auto form = [&](auto tc, auto fr) {
+    if (!ta && !tb) go(tc, std::false_type{}, std::false_type{}, fr);
+    else if (ta && !tb) go(tc, std::true_type{}, std::false_type{}, fr);
+    else if (!ta) go(tc, std::false_type{}, std::true_type{}, fr);
+    else go(tc, std::true_type{}, std::true_type{}, fr);
+  };
+  if (far) form(std::integral_constant<int, 64>{}, std::true_type{});
+  else if (big) form(std::integral_constant<int, 128>{}, std::false_type{});
+  else form(std::integral_constant<int, 64>{}, std::false_type{});
   return hipGetLastError();
 }
 
