@@ -14,6 +14,7 @@
 // through LDS in steps of 32.  Epilogues fuse bias, ReLU, the ReLU mask of the
 // backward pass and the BF16 conversion; weight gradients split the batch
 // dimension across workgroups and add FP32 partial tiles atomically.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -560,16 +561,19 @@ __device__ inline double pou_weight(const GridDesc& g, int i1, int i2, int i3, i
   return w;
 }
 
-// One workgroup per (cell, chunk of 64 columns); thread t: column t % 64,
-// node phase t / 64.  rho = RMS of the cell's residual column (over the
-// cell's F = np^3 node values, constrained nodes as 0); X0t[i][row] =
-// R[node_i][j] / rho as BF16 (rows i in [F, Fp) zero), Tt[i][row] =
-// E[node_i][j] / rho in FP32 when E is given (training targets).  The node
-// numbers and the per-node input and target factors of the cell are formed
-// once per workgroup in LDS (kMaxCellNodes entries), so the column loops only
-// load, scale and store.
+// One workgroup per (C cells, chunk of 64 columns); lane l of a wavefront: cell
+// l / k and column l % k of the C k <= 64 (cell, column) rows (C = 1: column l of
+// the chunk), wavefront ph: nodes i = ph, ph + 4, ...  rho = RMS of the cell's
+// residual column (over the cell's F = np^3 node values, constrained nodes as
+// 0); X0t[i][row] = R[node_i][j] / rho as BF16 (rows i in [F, Fp) zero),
+// Tt[i][row] = E[node_i][j] / rho in FP32 when E is given (training targets).
+// The node numbers and the per-node input and target factors of the cells are
+// formed once per workgroup in LDS, so the column loops only load, scale and
+// store.  Bound by memory; several cells per workgroup for few columns because
+// one cell's columns leave the other lanes idle and write X0t and Tt in pieces
+// (k = 16, p = 6, 8000 cells, with E: 470 -> 190 us).
 constexpr int kCols = 64;
-constexpr int kMaxCellNodes = 11 * 11 * 11;
+constexpr int kGatherNodeBytes = 2 * sizeof(double) + sizeof(int);  // LDS per (cell, node)
 
 // Per (cell, local node): the node number (-1 constrained), the input factor
 // sqrt(w)^[pou_sqrt] / sqrt(d) and sqrt(d) (d = dsc[node], 1 without dsc).
@@ -592,28 +596,36 @@ __device__ inline void cell_node_factors(const GridDesc& g, int np, int cx, int 
   }
 }
 
+template <bool MULTI>
 __global__ void __launch_bounds__(256)
-cell_gather_kernel(GridDesc g, int np, int k, const double* __restrict__ R, int64_t ldr,
+cell_gather_kernel(GridDesc g, int np, int k, int C_, const double* __restrict__ R, int64_t ldr,
                    const double* __restrict__ E, int64_t lde, int Fp, uint16_t* __restrict__ X0t,
                    float* __restrict__ Tt, int64_t ldx, float* __restrict__ rho, int pou_sqrt,
                    const double* __restrict__ dsc, int blocked) {
+  extern __shared__ double gather_sh[];
   __shared__ double part[256];
-  __shared__ int snode[kMaxCellNodes];
-  __shared__ double sfin[kMaxCellNodes], sdh[kMaxCellNodes];
-  const int e = blockIdx.x;
-  const int j0 = blockIdx.y * kCols;
+  const int F = np * np * np, ncells = g.n[0] * g.n[1] * g.n[2];
   const int t = threadIdx.x, jj = t % kCols, ph = t / kCols;
-  const int j = j0 + jj;
-  const int F = np * np * np;
-  const int cx = e % g.n[0], cy = (e / g.n[0]) % g.n[1], cz = e / (g.n[0] * g.n[1]);
-  cell_node_factors(g, np, cx, cy, cz, pou_sqrt, dsc, snode, sfin, sdh);
+  const int C = MULTI ? C_ : 1;
+  const int e0 = blockIdx.x * C, cells = MULTI ? min(C, ncells - e0) : 1;
+  // lanes past the last row take the first cell and the last column and store nothing
+  const bool jok = MULTI ? jj < cells * k : (int)(blockIdx.y * kCols) + jj < k;
+  const int c = MULTI && jok ? jj / k : 0, e = e0 + c;
+  const int j = jok ? (MULTI ? jj - c * k : (int)(blockIdx.y * kCols) + jj) : k - 1;
+  for (int u = 0; u < cells; ++u) {
+    const int cx = (e0 + u) % g.n[0], cy = ((e0 + u) / g.n[0]) % g.n[1],
+              cz = (e0 + u) / (g.n[0] * g.n[1]);
+    cell_node_factors(g, np, cx, cy, cz, pou_sqrt, dsc,
+                      reinterpret_cast<int*>(gather_sh + 2 * C * F) + u * F, gather_sh + u * F,
+                      gather_sh + (C + u) * F);
+  }
+  const double* sfin = gather_sh + c * F;
+  const double* sdh = gather_sh + (C + c) * F;
+  const int* snode = reinterpret_cast<const int*>(gather_sh + 2 * C * F) + c * F;
   __syncthreads();
   // Loads never sit behind a branch: constrained nodes and the padding rows
-  // read a valid element (clamped index) whose value a select then drops, and
-  // lanes past the last column read column k - 1 and store nothing; batches
-  // of kGatherBatch rows are loaded before they are used.
-  const bool jok = j < k;
-  const int jc = jok ? j : k - 1;
+  // read a valid element (clamped index) whose value a select then drops;
+  // batches of kGatherBatch rows are loaded before they are used.
   constexpr int kGatherBatch = 8;
   const int nrows = (Fp - ph + 3) / 4;  // rows i = ph, ph + 4, ... < Fp of this wavefront
   auto node_of = [&](int i) { return snode[i < F ? i : F - 1]; };
@@ -625,7 +637,7 @@ cell_gather_kernel(GridDesc g, int np, int k, const double* __restrict__ R, int6
 #pragma unroll
       for (int u = 0; u < kGatherBatch; ++u) {
         const int node = node_of(ph + 4 * (r0 + u));
-        xv[u] = R[(int64_t)(node >= 0 ? node : 0) * ldr + jc];
+        xv[u] = R[(int64_t)(node >= 0 ? node : 0) * ldr + j];
       }
 #pragma unroll
       for (int u = 0; u < kGatherBatch; ++u) {
@@ -866,25 +878,50 @@ node_assemble_kernel(AsmArgs a, int nlines, int nchunks) {
 
 // dYt = 2 scale w[n] (Yt - Tt) for features < F (0 for the padding), as
 // BF16; loss += scale sum w[n] (Yt - Tt)^2 (w = 1 when the row weights are
-// null).
+// null).  Pieces of one feature by 4 x 256 batch rows, 16-byte loads and 8-byte
+// stores where VEC says that every row starts on such a boundary.  Bound by
+// memory (344 x 128000: 92 us, 4.8 TB/s).
+template <bool VEC>
 __global__ void __launch_bounds__(256)
 mse_grad_kernel(int F, int Fp, int64_t nrows, const float* __restrict__ Yt,
                 const float* __restrict__ Tt, int64_t ld, const float* __restrict__ roww,
                 float scale, uint16_t* __restrict__ dYt, double* __restrict__ loss) {
   __shared__ double part[256];
   double acc = 0.0;
-  const int64_t total = (int64_t)Fp * nrows;
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(idx / nrows);
-    const int64_t n = idx % nrows;
-    const float w = roww ? roww[n] : 1.0f;
-    float d = 0.f;
-    if (i < F) {
-      d = Yt[(int64_t)i * ld + n] - Tt[(int64_t)i * ld + n];
-      acc += (double)w * d * d;
+  const int64_t chunks = (nrows + 1023) / 1024, pieces = chunks * Fp;
+  for (int64_t u = blockIdx.x; u < pieces; u += gridDim.x) {
+    const int i = (int)(u / chunks);
+    const int64_t n = (u - i * chunks) * 1024 + 4 * threadIdx.x;
+    const int64_t o = (int64_t)i * ld + n;
+    if (VEC && n + 4 <= nrows) {
+      f32x4 w = {1.f, 1.f, 1.f, 1.f}, d = {0.f, 0.f, 0.f, 0.f};
+      if (roww) w = *reinterpret_cast<const f32x4*>(roww + n);
+      if (i < F) {
+        const f32x4 y = *reinterpret_cast<const f32x4*>(Yt + o);
+        const f32x4 x = *reinterpret_cast<const f32x4*>(Tt + o);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          d[r] = y[r] - x[r];
+          acc += (double)w[r] * d[r] * d[r];
+        }
+      }
+      ushort4 h;
+      h.x = f32_to_bf16(2.0f * scale * w[0] * d[0]);
+      h.y = f32_to_bf16(2.0f * scale * w[1] * d[1]);
+      h.z = f32_to_bf16(2.0f * scale * w[2] * d[2]);
+      h.w = f32_to_bf16(2.0f * scale * w[3] * d[3]);
+      *reinterpret_cast<ushort4*>(dYt + o) = h;
+    } else {
+      for (int r = 0; r < 4 && n + r < nrows; ++r) {
+        const float w = roww ? roww[n + r] : 1.0f;
+        float d = 0.f;
+        if (i < F) {
+          d = Yt[o + r] - Tt[o + r];
+          acc += (double)w * d * d;
+        }
+        dYt[o + r] = f32_to_bf16(2.0f * scale * w * d);
+      }
     }
-    dYt[(int64_t)i * ld + n] = f32_to_bf16(2.0f * scale * w * d);
   }
   part[threadIdx.x] = acc;
   __syncthreads();
@@ -895,17 +932,42 @@ mse_grad_kernel(int F, int Fp, int64_t nrows, const float* __restrict__ Yt,
   if (threadIdx.x == 0) unsafeAtomicAdd(loss, part[0] * (double)scale);
 }
 
-// out[m] (+)= sum_n X[m][n] (BF16 rows): bias gradients.
-__global__ void __launch_bounds__(256)
+// out[m] (+)= sum_n X[m][n] (BF16 rows): bias gradients.  One workgroup per row,
+// 16 bytes a load where VEC says that rows start on that boundary, four loads in
+// flight: 256 x 128000: 12 us (with 256 threads and single elements 131).
+constexpr int kRowThreads = 1024;
+template <bool VEC>
+__global__ void __launch_bounds__(kRowThreads)
 row_sums_kernel(int64_t N, const uint16_t* __restrict__ X, int64_t ld, float* __restrict__ out,
                 int accumulate) {
-  __shared__ float part[256];
+  __shared__ float part[kRowThreads];
   const int m = blockIdx.x;
-  float acc = 0.f;
-  for (int64_t n = threadIdx.x; n < N; n += blockDim.x) acc += bf16_to_f32(X[(int64_t)m * ld + n]);
-  part[threadIdx.x] = acc;
+  const uint16_t* row = X + (int64_t)m * ld;
+  const int64_t whole = VEC ? N / 8 : 0;  // chunks of 8
+  constexpr int U = 4;
+  float acc[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) acc[u] = 0.f;
+  auto add = [&](float& a, uint4 x) {
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      a += __uint_as_float(w[i] << 16) + __uint_as_float(w[i] & 0xffff0000u);
+  };
+  int64_t n = threadIdx.x;
+  for (; n + (U - 1) * kRowThreads < whole; n += U * kRowThreads) {
+    uint4 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      x[u] = *reinterpret_cast<const uint4*>(row + 8 * (n + u * kRowThreads));
+#pragma unroll
+    for (int u = 0; u < U; ++u) add(acc[u], x[u]);
+  }
+  for (; n < whole; n += kRowThreads) add(acc[0], *reinterpret_cast<const uint4*>(row + 8 * n));
+  for (n = 8 * whole + threadIdx.x; n < N; n += kRowThreads) acc[1] += bf16_to_f32(row[n]);
+  part[threadIdx.x] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
+  for (int s = kRowThreads / 2; s > 0; s >>= 1) {
     if (threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
     __syncthreads();
   }
@@ -1105,9 +1167,24 @@ hipError_t launch_cell_gather(const Operator& op, int k, const double* R, int64_
                               const double* E, int64_t lde, int Fp, uint16_t* X0t, float* Tt,
                               int64_t ldx, float* rho, int pou_sqrt, const double* dsc,
                               int blocked, hipStream_t s) {
-  dim3 grid((unsigned)op.ncells, (k + kCols - 1) / kCols);
-  hipLaunchKernelGGL(cell_gather_kernel, grid, dim3(256), 0, s, op.grid, op.np, k, R, ldr, E, lde,
-                     Fp, X0t, Tt, ldx, rho, pou_sqrt, dsc, blocked);
+  // Few columns: as many cells as fill the 64 lanes, up to 8 and to 64 KiB of LDS
+  // (p = 6, 4096 cells, with E: k = 1 173 -> 55 us, k = 8 167 -> 62, k = 32 260 ->
+  // 196; p = 10, one or two cells: k = 1 298 -> 245).
+  const int F = op.np * op.np * op.np;
+  int C = k < kCols ? kCols / k : 1;
+  C = std::min({C, 8, 65536 / (F * kGatherNodeBytes)});
+  if (C < 1) C = 1;
+  dim3 grid((unsigned)((op.ncells + C - 1) / C), C > 1 ? 1 : (k + kCols - 1) / kCols);
+  // One cell: LDS as if for the largest cell, six workgroups on a CU (eight of them
+  // take 95 instead of 91 us at p = 2, k = 64, 13824 cells).
+  const size_t lds = std::max<size_t>((size_t)C * F * kGatherNodeBytes, C > 1 ? 0 : 26640);
+  auto go = [&](auto multi) {
+    hipLaunchKernelGGL((cell_gather_kernel<decltype(multi)::value>), grid, dim3(256),
+                       lds, s, op.grid, op.np, k, C, R, ldr, E, lde,
+                       Fp, X0t, Tt, ldx, rho, pou_sqrt, dsc, blocked);
+  };
+  if (C > 1) go(std::true_type{});
+  else go(std::false_type{});
   return hipGetLastError();
 }
 
@@ -1169,16 +1246,27 @@ hipError_t launch_cell_scatter(const Operator& op, int k, const float* Yt, int64
 hipError_t launch_mse_grad(int F, int Fp, int64_t nrows, const float* Yt, const float* Tt,
                            int64_t ld, const float* roww, float scale, uint16_t* dYt, double* loss,
                            hipStream_t s) {
-  unsigned blocks = blocks_for((int64_t)Fp * nrows);
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(mse_grad_kernel, dim3(blocks), dim3(256), 0, s, F, Fp, nrows, Yt, Tt, ld, roww,
-                     scale, dYt, loss);
+  auto at = [](const void* p, size_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
+  const int64_t pieces = (nrows + 1023) / 1024 * Fp;
+  const dim3 grid((unsigned)std::min<int64_t>(pieces, 2048));  // one addition to loss each
+  if (ld % 4 == 0 && at(Yt, 16) && at(Tt, 16) && at(roww, 16) && at(dYt, 8))
+    hipLaunchKernelGGL((mse_grad_kernel<true>), grid, dim3(256), 0, s, F, Fp, nrows, Yt, Tt, ld,
+                       roww, scale, dYt, loss);
+  else
+    hipLaunchKernelGGL((mse_grad_kernel<false>), grid, dim3(256), 0, s, F, Fp, nrows, Yt, Tt, ld,
+                       roww, scale, dYt, loss);
   return hipGetLastError();
 }
 
 hipError_t launch_row_sums(int M, int64_t N, const uint16_t* X, int64_t ld, float* out,
                            bool accumulate, hipStream_t s) {
-  hipLaunchKernelGGL(row_sums_kernel, dim3(M), dim3(256), 0, s, N, X, ld, out, accumulate ? 1 : 0);
+  const bool vec = ld % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+  if (vec)
+    hipLaunchKernelGGL((row_sums_kernel<true>), dim3(M), dim3(kRowThreads), 0, s, N, X, ld, out,
+                       accumulate ? 1 : 0);
+  else
+    hipLaunchKernelGGL((row_sums_kernel<false>), dim3(M), dim3(kRowThreads), 0, s, N, X, ld, out,
+                       accumulate ? 1 : 0);
   return hipGetLastError();
 }
 
