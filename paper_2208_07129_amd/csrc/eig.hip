@@ -133,19 +133,25 @@ bj_norm_kernel(int K, const double* __restrict__ Aw, double* __restrict__ part, 
 // A serial chain of 63 rounds on one CU: what counts is the length of a round.
 // The 64 indices sit in 32 slot pairs (position t above position 63 - t) and
 // move one position per round, so every round reads and writes the same places:
-// the 2 x 2 block of slot pairs (i, j) takes the row rotation of pair i and the
+// the 2 x 2 block of slot pairs (i < j) takes the row rotation of pair i and the
 // column rotation of pair j at once and is stored at its place of the next
-// round (two LDS copies, four planes [slot][slot] of 32 x 32, so consecutive
-// lanes touch consecutive words).  Wavefront 0 forms a round's angles while the
-// others apply the round before to the rotation V.  Per round two barriers, one
-// pass over the block and two chains of reciprocal square roots (a division, two
-// square roots and two divisions, three barriers and separate row and column
-// passes before): 155 -> 63 us a launch.
-constexpr int kBjSweepThreads = 512;
-constexpr int kBjP2 = kBjPair / 2;                       // slot pairs
+// round (two LDS copies; four planes [slot][slot] of 32 x 32, of which the blocks
+// i < j are kept up: the matrix is symmetric).  The 13 wavefronts work side by
+// side with one barrier per round: wavefront 0 has the diagonal blocks in
+// registers and forms the next round's angles, for which it takes the two
+// elements that meet through this round's rotations by itself; eight rotate the
+// off-diagonal blocks, one per lane; four hold the rotation V in registers (lane =
+// row, a wavefront = eight slot pairs) and pass two columns each to their
+// neighbours.  The angle needs two chains of reciprocal square roots.  155 us a
+// launch with division, separate row and column passes and three barriers; 63
+// with the angles, the blocks and V one after the other; 35 so.
+constexpr int kBjP2 = kBjPair / 2;  // slot pairs
 constexpr int kBjPlane = kBjP2 * kBjP2;
-constexpr size_t kBjSweepLds =
-    (2 * 4 * (size_t)kBjPlane + 2 * 2 * (size_t)kBjPair * kBjP2) * sizeof(double);
+constexpr int kBjAWaves = 8, kBjVWaves = 4;  // wavefronts on the blocks, on V
+constexpr int kBjSweepThreads = 64 * (1 + kBjAWaves + kBjVWaves);
+constexpr size_t kBjSweepLds = 2 * 4 * (size_t)kBjPlane * sizeof(double);
+static_assert(kBjP2 * (kBjP2 - 1) / 2 <= 64 * kBjAWaves, "one off-diagonal block per lane");
+static_assert(2 * 4 * kBjPlane >= kBjPair * kBjLd, "V is written out through the blocks' LDS");
 
 // x^{-1/2} for x in [1/8, 4]: the hardware estimate and two Newton steps.
 __device__ __forceinline__ double rsqrt_unit(double x) {
@@ -185,16 +191,29 @@ __device__ __forceinline__ void jacobi_angle(double app, double aqq, double apq,
   s = (d == 0.0 ? 0.5 * fabs(b) : (d < 0.0 ? -0.5 : 0.5) * b) * rh * rc;
 }
 
+// Where the member of slot pair pr in slot (0 above, 1 below) goes next round.
+__device__ __forceinline__ void bj_next(int slot, int pr, int& ns, int& np) {
+  if (slot == 0) {
+    ns = pr == 1;  // position 1 -> 63
+    np = pr <= 1 ? 0 : pr - 1;
+  } else {
+    ns = pr < kBjP2 - 1;  // position 32 -> 31
+    np = pr < kBjP2 - 1 ? pr + 1 : kBjP2 - 1;
+  }
+}
+
 __global__ void __launch_bounds__(kBjSweepThreads)
 bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__ J,
                const BjState* __restrict__ st) {
   if (st->done != 0.0) return;
   extern __shared__ double sh[];
-  double* a = sh;                        // 2 copies of 4 planes
-  double* v = sh + 2 * 4 * kBjPlane;     // 2 copies of [slot][row][pair]
-  constexpr int VC = 2 * kBjPair * kBjP2, VS = kBjPair * kBjP2;
+  double* a = sh;  // 2 copies of 4 planes
   __shared__ double2 cs[2][kBjP2];
-  const int t = threadIdx.x, nb = K / kBj;
+  __shared__ double dg[2][2][kBjP2];              // rotated diagonal, [round][slot][pair]
+  __shared__ double xch[2][kBjVWaves][2][64];     // V's columns on their way to a neighbour
+  const int t = threadIdx.x, nb = K / kBj, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  constexpr int kRounds = kBjPair - 1;
   int P, Q;
   round_robin(nb, r, blockIdx.x, P, Q);
   for (int i = t; i < kBjPair * kBjPair; i += kBjSweepThreads) {
@@ -203,82 +222,146 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
     const int pi = si ? kBjPair - 1 - row : row, pj = sj ? kBjPair - 1 - col : col;
     a[(si * 2 + sj) * kBjPlane + pi * kBjP2 + pj] =
         Aw[(int64_t)pair_index(P, Q, row) * K + pair_index(P, Q, col)];
-    v[sj * VS + row * kBjP2 + pj] = row == col ? 1.0 : 0.0;
   }
   __syncthreads();
-  // where slot pair t's members go next round: above (0, t) and below (1, t)
-  auto next = [](int slot, int pr, int& ns, int& np) {
-    if (slot == 0) {
-      ns = pr == 1;                       // position 1 -> 63
-      np = pr == 0 ? 0 : (pr == 1 ? 0 : pr - 1);
-    } else {
-      ns = pr < kBjP2 - 1;                // position 32 -> 31
-      np = pr < kBjP2 - 1 ? pr + 1 : kBjP2 - 1;
-    }
-  };
-  for (int rr = 0; rr < kBjPair; ++rr) {
-    if (t < 64) {
-      if (t < kBjP2 && rr < kBjPair - 1) {
-        const double* ac = a + (rr & 1) * 4 * kBjPlane + t * (kBjP2 + 1);
-        const double top = ac[0], bot = ac[3 * kBjPlane];
-        // the items at the two positions this round; p is the smaller one
-        const int x0 = t == 0 ? 0 : 1 + (t - 1 + rr) % (kBjPair - 1);
-        const int x1 = 1 + (kBjPair - 2 - t + rr) % (kBjPair - 1);
-        double c, s;
-        jacobi_angle(x0 < x1 ? top : bot, x0 < x1 ? bot : top,
-                     ac[(x0 < x1 ? 1 : 2) * kBjPlane], c, s);
-        cs[rr & 1][t] = make_double2(c, x0 < x1 ? s : -s);
+  if (wave == 0) {
+    const int p = lane & (kBjP2 - 1);
+    double d0 = a[p * (kBjP2 + 1)], d1 = a[3 * kBjPlane + p * (kBjP2 + 1)];
+    double x = a[kBjPlane + p * (kBjP2 + 1)], c, s;
+    // items at the two positions; the angle is that of the smaller one first
+    int i0 = p == 0 ? 0 : p, i1 = kBjPair - 1 - p;
+    auto angle = [&]() {
+      const bool up = i0 < i1;
+      jacobi_angle(up ? d0 : d1, up ? d1 : d0, x, c, s);
+      s = up ? s : -s;
+    };
+    angle();
+    if (lane < kBjP2) cs[0][p] = make_double2(c, s);
+    __syncthreads();
+    // the members of slot pair p next round sit in (u, pu) and (w, pw) now
+    const int u = p == kBjP2 - 1 ? 1 : 0, pu = p == kBjP2 - 1 ? p : (p == 0 ? 0 : p + 1);
+    const int w = p == 0 ? 0 : 1, pw = p == 0 ? 1 : p - 1;
+    const bool sw = pu > pw;  // the blocks above the diagonal are kept
+    const int lo = sw ? pw : pu, hi = sw ? pu : pw;
+    const int m01 = sw ? 2 : 1, m10 = 3 - m01;  // plane of (slot of pu, slot of pw)
+    const double* blk = a + lo * kBjP2 + hi;
+    // the pair's own off-diagonal element, 0 now, goes to a block of the next round
+    int is, ip, js, jp;
+    bj_next(0, p, is, ip);
+    bj_next(1, p, js, jp);
+    double* zero = a + (is * 2 + js) * kBjPlane + ip * kBjP2 + jp;  // ip < jp
+    for (int rr = 0; rr + 1 < kRounds; ++rr) {
+      const double* ac = blk + (rr & 1) * 4 * kBjPlane;
+      const double m00 = ac[0], v01 = ac[m01 * kBjPlane], v10 = ac[m10 * kBjPlane],
+                   m11 = ac[3 * kBjPlane];
+      const double2 ru = cs[rr & 1][pu], rw = cs[rr & 1][pw];
+      // this round's rotation of the diagonal, handed on to the next places
+      const double cx = c * x, sx = s * x;
+      const double y0 = c * d0 - sx, y1 = s * d0 + cx;  // rows, first column
+      const double z0 = cx - s * d1, z1 = sx + c * d1;  // rows, second column
+      if (lane < kBjP2) {
+        dg[rr & 1][0][p] = c * y0 - s * z0;
+        dg[rr & 1][1][p] = s * y1 + c * z1;
+        zero[((rr + 1) & 1) * 4 * kBjPlane] = 0.0;
       }
-    } else if (rr > 0) {
-      const double* vc = v + ((rr - 1) & 1) * VC;
-      double* vn = v + (rr & 1) * VC;
-      for (int i = t - 64; i < kBjPair * kBjP2; i += kBjSweepThreads - 64) {
-        const int row = i / kBjP2, pj = i % kBjP2;
-        const double2 r2 = cs[(rr - 1) & 1][pj];
-        const double x = vc[i], y = vc[VS + i];
-        int s0, p0, s1, p1;
-        next(0, pj, s0, p0);
-        next(1, pj, s1, p1);
-        vn[s0 * VS + row * kBjP2 + p0] = r2.x * x - r2.y * y;
-        vn[s1 * VS + row * kBjP2 + p1] = r2.y * x + r2.x * y;
-      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const double a0 = u ? ru.y : ru.x, a1 = u ? ru.x : -ru.y;
+      const double b0 = w ? rw.y : rw.x, b1 = w ? rw.x : -rw.y;
+      const double e0 = fma(a0, m00, a1 * v10), e1 = fma(a0, v01, a1 * m11);
+      x = fma(b0, e0, b1 * e1);
+      d0 = dg[rr & 1][u][pu];
+      d1 = dg[rr & 1][w][pw];
+      i0 = p == 0 ? 0 : (i0 == kRounds ? 1 : i0 + 1);
+      i1 = i1 == kRounds ? 1 : i1 + 1;
+      angle();
+      if (lane < kBjP2) cs[(rr + 1) & 1][p] = make_double2(c, s);
+      __syncthreads();
     }
     __syncthreads();
-    if (rr < kBjPair - 1) {
-      const double* ac = a + (rr & 1) * 4 * kBjPlane;
-      double* an = a + ((rr + 1) & 1) * 4 * kBjPlane;
+    __syncthreads();
+  } else if (wave <= kBjAWaves) {
+    // off-diagonal block (pi, pj): rows r and 30 - r of the triangle fill 32 lanes
+    const int e = t - 64, fr = e / kBjP2, fk = e % kBjP2;
+    const bool upper = fk < kBjP2 - 1 - fr;
+    const int pi = upper ? fr : kBjP2 - 2 - fr, pj = upper ? fr + 1 + fk : fk;
+    const bool on = fr < kBjP2 / 2 - 1 || upper;
+    int to[2][2];
 #pragma unroll
-      for (int i = t; i < kBjPlane; i += kBjSweepThreads) {
-        const int pi = i / kBjP2, pj = i % kBjP2;
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        int is, ip, js, jp;
+        bj_next(u, pi, is, ip);
+        bj_next(w, pj, js, jp);
+        to[u][w] = ip <= jp ? (is * 2 + js) * kBjPlane + ip * kBjP2 + jp
+                            : (js * 2 + is) * kBjPlane + jp * kBjP2 + ip;
+      }
+    __syncthreads();
+    for (int rr = 0; rr + 1 < kRounds; ++rr) {
+      const double* ac = a + (rr & 1) * 4 * kBjPlane + pi * kBjP2 + pj;
+      double* an = a + ((rr + 1) & 1) * 4 * kBjPlane;
+      if (on) {
         const double2 ri = cs[rr & 1][pi], rj = cs[rr & 1][pj];
-        const double tt = ac[i], tb = ac[kBjPlane + i], bt = ac[2 * kBjPlane + i],
-                     bb = ac[3 * kBjPlane + i];
+        const double tt = ac[0], tb = ac[kBjPlane], bt = ac[2 * kBjPlane], bb = ac[3 * kBjPlane];
         // rows: (top, bottom) <- (c top - s bottom, s top + c bottom), then columns
         const double x0 = ri.x * tt - ri.y * bt, y0 = ri.x * tb - ri.y * bb;
         const double x1 = ri.y * tt + ri.x * bt, y1 = ri.y * tb + ri.x * bb;
-        int is[2], ip[2], js[2], jp[2];
-        next(0, pi, is[0], ip[0]);
-        next(1, pi, is[1], ip[1]);
-        next(0, pj, js[0], jp[0]);
-        next(1, pj, js[1], jp[1]);
-        auto put = [&](int u, int w, double x) {
-          an[(is[u] * 2 + js[w]) * kBjPlane + ip[u] * kBjP2 + jp[w]] = x;
-        };
-        put(0, 0, rj.x * x0 - rj.y * y0);
-        put(0, 1, rj.y * x0 + rj.x * y0);
-        put(1, 0, rj.x * x1 - rj.y * y1);
-        put(1, 1, rj.y * x1 + rj.x * y1);
+        an[to[0][0]] = rj.x * x0 - rj.y * y0;
+        an[to[0][1]] = rj.y * x0 + rj.x * y0;
+        an[to[1][0]] = rj.x * x1 - rj.y * y1;
+        an[to[1][1]] = rj.y * x1 + rj.x * y1;
       }
+      __syncthreads();
+    }
+    __syncthreads();
+    __syncthreads();
+  } else {
+    constexpr int G = kBjP2 / kBjVWaves;  // slot pairs of a wavefront
+    const int g = wave - 1 - kBjAWaves;
+    double top[G], bot[G];
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      top[k] = lane == G * g + k ? 1.0 : 0.0;
+      bot[k] = lane == kBjPair - 1 - (G * g + k) ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    for (int rr = 0; rr < kRounds; ++rr) {
+#pragma unroll
+      for (int k = 0; k < G; ++k) {
+        const double2 q = cs[rr & 1][G * g + k];
+        const double x = top[k], y = bot[k];
+        top[k] = q.x * x - q.y * y;
+        bot[k] = q.y * x + q.x * y;
+      }
+      xch[rr & 1][g][0][lane] = top[0];
+      xch[rr & 1][g][1][lane] = bot[G - 1];
+      __syncthreads();
+      // one position on: tops to the left, bottoms to the right
+      const double t0 = top[0], t1 = top[1], bl = bot[G - 1];
+#pragma unroll
+      for (int k = 0; k + 1 < G; ++k) top[k] = top[k + 1];
+#pragma unroll
+      for (int k = G - 1; k > 0; --k) bot[k] = bot[k - 1];
+      if (g == kBjVWaves - 1) top[G - 1] = bl;
+      else top[G - 1] = xch[rr & 1][g + 1][0][lane];
+      if (g == 0) {
+        top[0] = t0;
+        bot[0] = t1;
+      } else {
+        bot[0] = xch[rr & 1][g - 1][1][lane];
+      }
+    }
+    // after 63 rounds every index is back at its own position
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      a[lane * kBjLd + G * g + k] = top[k];
+      a[lane * kBjLd + kBjPair - 1 - (G * g + k)] = bot[k];
     }
     __syncthreads();
   }
-  // after 63 rounds every index is back at its own position
-  const double* vf = v + ((kBjPair - 1) & 1) * VC;
   double* out = J + (int64_t)blockIdx.x * kBjPair * kBjPair;
-  for (int i = t; i < kBjPair * kBjPair; i += kBjSweepThreads) {
-    const int row = i / kBjPair, col = i % kBjPair;
-    out[i] = col < kBjP2 ? vf[row * kBjP2 + col] : vf[VS + row * kBjP2 + kBjPair - 1 - col];
-  }
+  for (int i = t; i < kBjPair * kBjPair; i += kBjSweepThreads)
+    out[i] = a[(i / kBjPair) * kBjLd + i % kBjPair];
 }
 
 // The round's rotation applied to the matrix and to the eigenvectors.
@@ -286,15 +369,22 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
 // of pair j, replaced by J_i^T piece J_j.  Workgroups [np^2, np^2 + np K/64):
 // rows 64 rb .. 64 rb + 63 of V in the columns of pair j, replaced by
 // piece J_j.  The pieces are disjoint, so the update is in place.
-// Bound by the LDS reads of the products (6 bytes per multiply-add); 512 threads
-// instead of 256 hide more of the loads: 24 -> 16.5 us at K = 256.
-constexpr int kBjUpdThreads = 512;
+//
+// Matrix cores (v_mfma_f64_16x16x4f64: A[i][c] in lane i + 16 c, B[c][j] in lane
+// j + 16 c, D[i][j] in lane j + 16 (i mod 4), register i / 4).  A wavefront forms
+// 16 columns of the result: first of piece J_j, whose registers are then the
+// operand B of J_i^T times it, so nothing but the piece (transposed) and the
+// rotations passes through LDS.  Bound by the two products at the matrix cores'
+// rate on as many CUs as there are pieces: K = 256, 24 us with 256 threads on the
+// vector ALUs (6 bytes of LDS per multiply-add), 16.5 with 512, 14.8 so.
+constexpr int kBjUpdThreads = 256;
+typedef double v4d __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(kBjUpdThreads)
 bj_update_kernel(int K, int r, double* __restrict__ Aw, double* __restrict__ Vw,
                  const double* __restrict__ J, const BjState* __restrict__ st) {
   if (st->done != 0.0) return;
   extern __shared__ double sh[];
-  double* B = sh;                       // the piece (then J_i^T piece)
+  double* Bt = sh;                      // the piece, transposed
   double* Ji = sh + kBjPair * kBjLd;
   double* Jj = sh + 2 * kBjPair * kBjLd;
   const int t = threadIdx.x, nb = K / kBj, np = nb / 2;
@@ -320,60 +410,47 @@ bj_update_kernel(int K, int r, double* __restrict__ Aw, double* __restrict__ Vw,
     const int e = e0 + t;
     const int row = e / kBjPair, col = e % kBjPair;
     const int grow = on_a ? pair_index(Pi, Qi, row) : rb * kBjPair + row;
-    B[row * kBjLd + col] = base[(int64_t)grow * K + pair_index(Pj, Qj, col)];
+    Bt[col * kBjLd + row] = base[(int64_t)grow * K + pair_index(Pj, Qj, col)];
     Jj[row * kBjLd + col] = jj[e];
     if (on_a) Ji[row * kBjLd + col] = ji[e];
   }
   __syncthreads();
-  // thread (ty, tx): rows ty + 32 u, columns tx + 16 w of the 64 x 64 result
-  const int ty = t / 16, tx = t % 16;
-  double acc[2][4];
-  if (on_a) {  // B := J_i^T B
+  const int lane = t & 63, l16 = lane & 15, c4 = lane >> 4, n0 = (t >> 6) * 16;
+  // M^T (16 columns of N): tile m of rows, operands M[b][row], N[b][column]
+  v4d p[4];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+  for (int m = 0; m < 4; ++m) p[m] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int b = 0; b < kBjPair; b += 4) {
+    const double y = Jj[(b + c4) * kBjLd + n0 + l16];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) acc[u][w] = 0.0;
-    for (int b = 0; b < kBjPair; ++b) {
-      double x[2], y[4];
+    for (int m = 0; m < 4; ++m)
+      p[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Bt[(b + c4) * kBjLd + 16 * m + l16], y, p[m], 0,
+                                                  0, 0);
+  }
+  if (on_a) {
+    v4d q[4];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) x[u] = Ji[b * kBjLd + ty + 32 * u];
+    for (int m = 0; m < 4; ++m) q[m] = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int w = 0; w < 4; ++w) y[w] = B[b * kBjLd + tx + 16 * w];
+    for (int b = 0; b < kBjPair; b += 4) {  // rows b .. b + 3 of the first product
+      const double y = p[b / 16][(b / 4) % 4];
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) acc[u][w] = fma(x[u], y[w], acc[u][w]);
+      for (int m = 0; m < 4; ++m)
+        q[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ji[(b + c4) * kBjLd + 16 * m + l16], y, q[m],
+                                                    0, 0, 0);
     }
-    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) B[(ty + 32 * u) * kBjLd + tx + 16 * w] = acc[u][w];
-    __syncthreads();
+    for (int m = 0; m < 4; ++m) p[m] = q[m];
   }
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
+  for (int m = 0; m < 4; ++m)
 #pragma unroll
-    for (int w = 0; w < 4; ++w) acc[u][w] = 0.0;
-  for (int b = 0; b < kBjPair; ++b) {  // B J_j
-    double x[2], y[4];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) x[u] = B[(ty + 32 * u) * kBjLd + b];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) y[w] = Jj[b * kBjLd + tx + 16 * w];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) acc[u][w] = fma(x[u], y[w], acc[u][w]);
-  }
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int row = ty + 32 * u;
-    const int grow = on_a ? pair_index(Pi, Qi, row) : rb * kBjPair + row;
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-      base[(int64_t)grow * K + pair_index(Pj, Qj, tx + 16 * w)] = acc[u][w];
-  }
+    for (int u = 0; u < 4; ++u) {
+      const int row = 16 * m + 4 * u + c4;
+      const int grow = on_a ? pair_index(Pi, Qi, row) : rb * kBjPair + row;
+      base[(int64_t)grow * K + pair_index(Pj, Qj, n0 + l16)] = p[m][u];
+    }
 }
 
 // Eigenvalues ascending by rank (ties by index), eigenvector columns moved to
@@ -439,7 +516,8 @@ hipError_t launch_sym_eig_blocked(int k, const double* A, int64_t lda, double* w
   double* J = Vw + (int64_t)K * K;
   const size_t lds_upd = 3 * (size_t)kBjPair * kBjLd * sizeof(double);
   KernelFacts f;  // raise the dynamic LDS limits on this device
-  hipError_t err = kernel_facts(reinterpret_cast<const void*>(bj_pair_kernel), kBjSweepThreads, kBjSweepLds, f);
+  hipError_t err = kernel_facts(reinterpret_cast<const void*>(bj_pair_kernel), kBjSweepThreads,
+                                kBjSweepLds, f);
   if (err == hipSuccess)
     err = kernel_facts(reinterpret_cast<const void*>(bj_update_kernel), kBjUpdThreads, lds_upd, f);
   if (err != hipSuccess) return err;
@@ -452,10 +530,10 @@ hipError_t launch_sym_eig_blocked(int k, const double* A, int64_t lda, double* w
   const unsigned upd_blocks = (unsigned)(np * np + (K / kBjPair) * np);
   for (int sweep = 0; sweep < kBjMaxSweeps; ++sweep) {
     for (int r = 0; r < nb - 1; ++r) {
-      hipLaunchKernelGGL(bj_pair_kernel, dim3(np), dim3(kBjSweepThreads), kBjSweepLds, s, K, r, Aw, J,
-                         st);
-      hipLaunchKernelGGL(bj_update_kernel, dim3(upd_blocks), dim3(kBjUpdThreads), lds_upd, s, K, r, Aw,
-                         Vw, J, st);
+      hipLaunchKernelGGL(bj_pair_kernel, dim3(np), dim3(kBjSweepThreads), kBjSweepLds, s, K, r, Aw,
+                         J, st);
+      hipLaunchKernelGGL(bj_update_kernel, dim3(upd_blocks), dim3(kBjUpdThreads), lds_upd, s, K, r,
+                         Aw, Vw, J, st);
     }
     hipLaunchKernelGGL(bj_norm_kernel, norm_grid, dim3(kBjNormThreads), 0, s, K, Aw, J, st, 0);
   }
