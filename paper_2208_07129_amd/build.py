@@ -60,8 +60,9 @@ def jobs():
         out.append(("apply_box.hip", f"apply_box_p{p}.o", [f"-DMF_P={p}"]))
         if p <= 6:
             # matrix-core results straight in the vector registers that read them
-            out.append(("apply_pair.hip", f"apply_pair_p{p}.o",
-                        [f"-DMF_P={p}", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]))
+            for src in ("apply_pair", "apply_cheb_pair"):
+                out.append((f"{src}.hip", f"{src}_p{p}.o",
+                            [f"-DMF_P={p}", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]))
         if p <= 7:
             out.append(("apply_mfma.hip", f"apply_mfma_p{p}.o", [f"-DMF_P={p}"]))
         out.append(("apply_mixed.hip", f"apply_mixed_p{p}.o", [f"-DMF_P={p}"]))

@@ -48,10 +48,14 @@ int mf_cheb_step(mf_operator* handle, const double* D, const double* Y, const do
   if (Xp && Xp != Out && overlaps(Out, span, Xp, span))
     return fail(MF_ERR_ARG, "Xp must be Out itself or not overlap it");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t err = launch_cheb_init(*op, Y, Xp, Out, ld, nvec, b, c, s);
+  const PairPlan plan = cheb_pair_plan(*op, nvec, (int64_t)span);
+  const bool pair = plan.items > 0;
+  hipError_t err = launch_cheb_init(*op, Y, Xp, Out, ld, nvec, b, c,
+                                    pair ? op->p * plan.len : op->p, s);
   if (err != hipSuccess) return hip_fail(err, "Chebyshev init kernel launch");
   const ChebArgs ca{D, Xp, a, b, c};
-  err = launch_apply_cheb(*op, Y, Out, ld, nvec, ca, s);
+  err = pair ? launch_cheb_pair(*op, Y, Out, ld, nvec, ca, plan, s)
+             : launch_apply_cheb(*op, Y, Out, ld, nvec, ca, s);
   if (err != hipSuccess) return hip_fail(err, "Chebyshev step kernel launch");
   return MF_OK;
 }

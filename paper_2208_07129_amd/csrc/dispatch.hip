@@ -78,11 +78,11 @@ __global__ void zero_shared_rows_kernel(double* __restrict__ Y, int Nx, int Ny, 
 // (cell-interior rows are written by the fused kernel) get b Y + c Xp, and
 // constrained rows (the boundary of a zero-Dirichlet mesh) 0.
 __global__ void cheb_init_kernel(const double* __restrict__ Y, const double* Xp, double* Out,
-                                 int Nx, int Ny, int Nz, int p, int dirichlet, int ncols,
-                                 int64_t ld, double b, double c) {
+                                 int Nx, int Ny, int Nz, int p, int py, int ylast, int dirichlet,
+                                 int ncols, int64_t ld, double b, double c) {
   const int line = blockIdx.x;
   const int gy = line % Ny, gz = line / Ny;
-  const bool full = (gy % p == 0) || (gz % p == 0);
+  const bool full = (gy % py == 0) || gy == ylast || (gz % p == 0);
   const bool yz_bnd = dirichlet && (gy == 0 || gy == Ny - 1 || gz == 0 || gz == Nz - 1);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int step = full ? 1 : p;
@@ -221,6 +221,11 @@ int batched_blocks_per_cu(int prec, int bcfg) {
   return 0;
 }
 
+// The last plane of nodes in y where it is a cell face of its own (free direction).
+static int last_face_y(const int64_t* nodes, int p) {
+  return nodes[1] % p == 1 || p == 1 ? (int)nodes[1] - 1 : -1;
+}
+
 hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int py, int ncols,
                                    int64_t ld, hipStream_t s) {
   const int64_t lines = nodes[1] * nodes[2];
@@ -234,17 +239,17 @@ hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int
   if (wgs > lines) wgs = lines;
   hipLaunchKernelGGL(zero_shared_rows_kernel, dim3((unsigned)wgs), dim3(256), 0, s, Y,
                      (int)nodes[0], (int)nodes[1], p, py,
-                     nodes[1] % p == 1 || p == 1 ? (int)nodes[1] - 1 : -1, ncols, ld, lines, cw_log2);
+                     last_face_y(nodes, p), ncols, ld, lines, cw_log2);
   return hipGetLastError();
 }
 
 hipError_t launch_cheb_init(const Operator& op, const double* Y, const double* Xp, double* Out,
-                            int64_t ld, int nvec, double b, double c, hipStream_t s) {
+                            int64_t ld, int nvec, double b, double c, int py, hipStream_t s) {
   const int64_t lines = op.nodes[1] * op.nodes[2];
   if (lines < 1) return hipSuccess;
   hipLaunchKernelGGL(cheb_init_kernel, dim3((unsigned)lines), dim3(256), 0, s, Y, Xp, Out,
-                     (int)op.nodes[0], (int)op.nodes[1], (int)op.nodes[2], op.p, op.grid.dirichlet,
-                     nvec, ld, b, c);
+                     (int)op.nodes[0], (int)op.nodes[1], (int)op.nodes[2], op.p, py,
+                     last_face_y(op.nodes, op.p), op.grid.dirichlet, nvec, ld, b, c);
   return hipGetLastError();
 }
 
@@ -483,9 +488,9 @@ bool pair_chosen(const Operator& op, int nvec) {
 // rows between consecutive cells, and a wavefront's first cell has nothing to
 // hide its loads behind; the estimate is rounds of resident wavefronts times
 // (cells of a segment + that start).
-PairPlan pair_plan(const Operator& op, int nvec) {
+PairPlan pair_plan(const Operator& op, int nvec, int cols) {
   PairPlan b{};
-  b.cols = pair_columns(nvec);
+  b.cols = cols > 0 ? cols : pair_columns(nvec);
   b.ntiles = (nvec + b.cols - 1) / b.cols;
   const int lx = pair_cells(b.cols);
   b.nxg = (op.grid.n[0] + lx - 1) / lx;
@@ -509,6 +514,40 @@ PairPlan pair_plan(const Operator& op, int nvec) {
   b.items = items < (1LL << 30) ? (int)items : 0;
   b.chunk = (items + 7) / 8;
   return b;
+}
+
+// The Chebyshev step in the register-resident form: asked for (shape 0), or the
+// built-in choice where it wins.  Measured with the initialisation, box kernel
+// against this, at cells-times-tiles per resident wavefront: p = 6, 16^3 cells, 16
+// columns (4) 206 against 186 us, 64 (16) 801 / 557, 8^3 cells, 64 (2) 97 / 100;
+// p = 4, 24^3, 16 (6.8) 242 / 237, 64 (27) 898 / 677, 10^3, 128 (3.9) 109 / 124; p = 3,
+// 24^3, 12 (6.8) 140 / 127, 16 (6.8) 121 / 128, 32 (13.5) 197 / 188; q = 6: 14^3, 16
+// (2.7) 95 / 101, 64 (10.7) 316 / 296; p = 2, 32^3, 8 88 / 107, 16 (8) 129 / 113, 16^3,
+// 16 (1) 33 / 34, 64 (4) 66 / 58.
+PairPlan cheb_pair_plan(const Operator& op, int nvec, int64_t span) {
+  if (op.nq > 7 || op.deterministic || op.cfg > 0 || span >= kPairMaxSpan ||
+      op.ndofs * 8 >= kPairMaxSpan)
+    return PairPlan{};
+  const PairPlan plan = pair_plan(op, nvec, 16);
+  if (op.cfg == 0) return plan;
+  const double steps = (double)op.ncells * plan.ntiles / (1024.0 * pair_waves(op.nq));
+  const double least = op.nq <= 3   ? 2.0
+                       : op.nq == 7 ? 4.0
+                       : op.nq == 5 || (op.nq == 4 && nvec % 8 != 0) ? 6.0 : 10.0;
+  return nvec > 8 && steps >= least ? plan : PairPlan{};
+}
+
+hipError_t launch_cheb_pair(const Operator& op, const double* Y, double* Out, int64_t ld, int nvec,
+                            const ChebArgs& ca, const PairPlan& plan, hipStream_t s) {
+  switch (op.p) {
+    case 1: return launch_cheb_pair_p<1>(op, Y, Out, ld, nvec, ca, plan, s);
+    case 2: return launch_cheb_pair_p<2>(op, Y, Out, ld, nvec, ca, plan, s);
+    case 3: return launch_cheb_pair_p<3>(op, Y, Out, ld, nvec, ca, plan, s);
+    case 4: return launch_cheb_pair_p<4>(op, Y, Out, ld, nvec, ca, plan, s);
+    case 5: return launch_cheb_pair_p<5>(op, Y, Out, ld, nvec, ca, plan, s);
+    case 6: return launch_cheb_pair_p<6>(op, Y, Out, ld, nvec, ca, plan, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_apply_pair(const Operator& op, const ApplyLaunch& a, const PairPlan& plan,

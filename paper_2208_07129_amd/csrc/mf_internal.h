@@ -148,9 +148,9 @@ struct ChebArgs {
 hipError_t launch_apply_cheb(const Operator& op, const double* Y, double* Out, int64_t ld,
                              int nvec, const ChebArgs& ca, hipStream_t s);
 // Face rows of Out := b Y + c Xp (0 on constrained rows): the part of a
-// Chebyshev step that the apply's atomics add to.
+// Chebyshev step that the apply's atomics add to (y faces every py nodes).
 hipError_t launch_cheb_init(const Operator& op, const double* Y, const double* Xp, double* Out,
-                            int64_t ld, int nvec, double b, double c, hipStream_t s);
+                            int64_t ld, int nvec, double b, double c, int py, hipStream_t s);
 // out[node] := GLL-lumped mass diagonal (or its inverse square root, 0 on
 // constrained rows).
 hipError_t launch_gll_mass(const Operator& op, int inv_sqrt, double* out, hipStream_t s);
@@ -261,7 +261,11 @@ hipError_t launch_apply_box(const Operator& op, const ApplyLaunch& a, hipStream_
 constexpr int64_t kPairMaxSpan = 0xF0000000LL;
 bool pair_built(int q);
 bool pair_chosen(const Operator& op, int nvec);
-PairPlan pair_plan(const Operator& op, int nvec);
+PairPlan pair_plan(const Operator& op, int nvec, int cols = 0);  // cols 0: by nvec
+// Its Chebyshev step: no items where it is not taken; span: bytes of a multivector.
+PairPlan cheb_pair_plan(const Operator& op, int nvec, int64_t span);
+hipError_t launch_cheb_pair(const Operator& op, const double* Y, double* Out, int64_t ld, int nvec,
+                            const ChebArgs& ca, const PairPlan& plan, hipStream_t s);
 hipError_t launch_apply_pair(const Operator& op, const ApplyLaunch& a, const PairPlan& plan,
                              hipStream_t s);
 // FP64 matrix-core body (shape 10: 8 columns per item).

@@ -539,6 +539,9 @@ constexpr int pair_columns(int nvec) {
   return nvec > 8 ? 16 : nvec > 4 ? 8 : nvec > 2 ? 4 : nvec;
 }
 template <int P>
+hipError_t launch_cheb_pair_p(const Operator& op, const double* Y, double* Out, int64_t ld,
+                              int nvec, const ChebArgs& ca, const PairPlan& plan, hipStream_t s);
+template <int P>
 hipError_t launch_apply_pair_p(const Operator& op, const ApplyLaunch& a, const PairPlan& plan,
                                hipStream_t s);
 template <int P>
