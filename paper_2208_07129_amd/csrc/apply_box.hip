@@ -13,7 +13,7 @@
 namespace mf {
 namespace {
 
-template <int NP, int NQ, int B, int C, int NT, bool ACCUM>
+template <int NP, int NQ, int B, int C, int NT, bool ACCUM, bool ROWS>
 __global__ void __attribute__((amdgpu_flat_work_group_size(1, NT),
                                amdgpu_waves_per_eu(box_waves_per_eu(NP, NQ, B, NT))))
 apply_box_kernel(const GridDesc grid, const int32_t* __restrict__ order,
@@ -25,7 +25,8 @@ apply_box_kernel(const GridDesc grid, const int32_t* __restrict__ order,
   if (item >= nitems) return;
   const int64_t e = order[item / ntiles];
   const int v0 = (int)(item % ntiles) * B;
-  box_cell_tile<NP, NQ, B, C, NT, ACCUM>(lds, grid, geo, vq, X, Y, ldx, ldy, nvec, e, v0);
+  box_cell_tile<NP, NQ, B, C, NT, ACCUM, double, ROWS>(lds, grid, geo, vq, X, Y, ldx, ldy, nvec, e,
+                                                       v0);
 }
 
 // Persistent grid: the workgroups of each XCD take that XCD's contiguous item
@@ -56,9 +57,18 @@ hipError_t launch_box(const ApplyLaunch& a, hipStream_t s) {
   static_assert(lds <= kLdsMax, "LDS");
   using Kern = void (*)(const GridDesc, const int32_t*, const double*, const double*,
                        const double*, double*, int64_t, int64_t, int, int, int64_t, int64_t);
+  // Assembly along the rows (box_p8_rows): its extra LDS stage lengthens a lone
+  // item, so tiles of four columns and cells of nine points take it only on meshes
+  // that fill the chip.  Without and with it, one column: p = 6, 16^3 72 / 47 us, 6^3
+  // 20 / 18; p = 8, 12^3 62 / 43, 4^3 19 / 20; two: p = 8, 12^3 62 / 54, 4^3 19 / 22;
+  // four: p = 6, 16^3 75 / 69, 6^3 19 / 20; p = 4, 24^3 93 / 85; p = 8, 12^3 70 / 78.
+  constexpr bool rows_built = !PERS && C == 1 && B <= (NP >= 9 ? 2 : 4);
+  constexpr int64_t rows_min = B <= 2 && NP <= 8 ? 0 : 1024;
   Kern k;
   if constexpr (PERS) k = apply_box_pers_kernel<NP, NQ, B, C, NT, ACCUM>;
-  else k = apply_box_kernel<NP, NQ, B, C, NT, ACCUM>;
+  else k = apply_box_kernel<NP, NQ, B, C, NT, ACCUM, false>;
+  if constexpr (rows_built)
+    if (nitems >= rows_min) k = apply_box_kernel<NP, NQ, B, C, NT, ACCUM, true>;
   KernelFacts f;
   hipError_t err = kernel_facts(reinterpret_cast<const void*>(k), NT, lds, f);
   if (err != hipSuccess) return err;

@@ -471,6 +471,53 @@ __device__ __forceinline__ void box_p8(const T* __restrict__ bB,
   }
 }
 
+// The same for narrow tiles (B columns, C = 1, FP64): the results pass through LDS
+// (bA, which nobody reads any more) and are assembled with the nodes of a pencil on
+// neighbouring lanes.  The additions of a wavefront are bound by the number of
+// memory rows they touch: with lanes over pencils every lane's node lies in its
+// own row (p = 6, 16^3 cells, one column, with the zero fill: 72 -> 47 us; p = 4,
+// 24^3: 97 -> 55).
+template <int NP, int NQ, int B, int NT, bool ACCUM>
+__device__ __forceinline__ void box_p8_rows(const double* __restrict__ bB,
+                                            double* __restrict__ bA, const GridDesc& gd,
+                                            double* __restrict__ Y, int64_t ldy, int nvec, int64_t e,
+                                            int v0, int tid) {
+  using GT = BoxGather<NP, B, 1, NT, double>;
+  constexpr int R1 = GT::R1, NP3 = NP * NP * NP;
+  double t[R1][NQ], o[R1][NP];
+#pragma unroll
+  for (int k = 0; k < R1; ++k) {
+    const int w = GT::TK::clamp(tid + k * NT), g = w % B, pen = w / B;
+    const int base = ((pen % NP) + NQ * (pen / NP)) * NQ;  // (j, k) in the NQ-strided layout
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) t[k][q] = bB[(base + q) * B + g];
+  }
+  eo_matvec<MatN<NP, NQ>, NP, NQ, true, NP, R1>(t, o);
+#pragma unroll
+  for (int k = 0; k < R1; ++k) {
+    const int w = tid + k * NT;
+    if (w >= GT::T1) continue;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) bA[((w / B) * NP + i) * B + w % B] = o[k][i];
+  }
+  __syncthreads();
+  const int ei = (int)e;
+  const int cx = ei % gd.n[0], cy = (ei / gd.n[0]) % gd.n[1], cz = ei / (gd.n[0] * gd.n[1]);
+  auto inner = [](int i) { return i > 0 && i < NP - 1; };
+#pragma unroll
+  for (int u0 = 0; u0 < NP3 * B; u0 += NT) {
+    const int u = u0 + tid, v = v0 + u % B, n = u / B;
+    const int i = n % NP, j = n / NP % NP, k = n / (NP * NP);
+    if (u >= NP3 * B || v >= nvec) continue;
+    const int node = grid_node(gd, cx, cy, cz, i, j, k);
+    if (node < 0) continue;
+    double* dst = Y + (int64_t)node * ldy + v;
+    const double y = bA[u];
+    if (!(inner(i) && inner(j) && inner(k))) unsafeAtomicAdd(dst, y);
+    else if (ACCUM) *dst += y;
+    else *dst = y;
+  }
+}
 // Persistent form of the item loop: the workgroup owns items it0, it0 + W,
 // ... < end (cell = order[item / ntiles], columns (item % ntiles) B ..).  The
 // X values (and scaled potential) of item i+1 are loaded into registers while
@@ -545,7 +592,7 @@ __device__ __forceinline__ void box_items(T* __restrict__ lds, const GridDesc& g
 // One (cell e, columns v0 .. v0+B-1) work item.  `lds` holds
 // box_lds_bytes_t<T>(NP, NQ, B) bytes; the caller synchronises the workgroup
 // before reusing it for another item.
-template <int NP, int NQ, int B, int C, int NT, bool ACCUM, typename T = double>
+template <int NP, int NQ, int B, int C, int NT, bool ACCUM, typename T = double, bool ROWS = false>
 __device__ __forceinline__ void box_cell_tile(T* __restrict__ lds, const GridDesc& grid,
                                               const double* __restrict__ geo,
                                               const double* __restrict__ vq,
@@ -567,7 +614,10 @@ __device__ __forceinline__ void box_cell_tile(T* __restrict__ lds, const GridDes
   box_p1<NP, NQ, B, C, NT, T>(bA, Gt, tid);
   __syncthreads();
   box_mid<NP, NQ, B, C, NT, T>(bA, bB, svq, g0, g1, g2, tid);
-  box_p8<NP, NQ, B, C, NT, ACCUM, T>(bB, Gt, Y, ldy, nvec, v0, tid);
+  if constexpr (ROWS)
+    box_p8_rows<NP, NQ, B, NT, ACCUM>(bB, bA, grid, Y, ldy, nvec, e, v0, tid);
+  else
+    box_p8<NP, NQ, B, C, NT, ACCUM, T>(bB, Gt, Y, ldy, nvec, v0, tid);
 }
 
 // ------------------------------------------------ Chebyshev filter step
