@@ -217,6 +217,10 @@ def basis_1d(p: int, q: int) -> dict:
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
         import torch
+        # the current stream's handle without a Stream object: 0.5 instead of 3.2 us, of
+        # the 11 us that the host spends on a smallest apply
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if hasattr(stream, "cuda_stream"):
         return stream.cuda_stream
