@@ -4,11 +4,14 @@
 //
 // One workgroup per (set, 64-column tile, chunk of the set's slaves): lane =
 // column, so every row access is one contiguous 512-byte segment of a
-// dof-major multivector, and the weights are wave-uniform (one W_I row or
-// column per wave step).  A set has up to (2p+1)^2 slaves, so the slave chunks
+// dof-major multivector.  A set has up to (2p+1)^2 slaves, so the slave chunks
 // give the launch several workgroups per set (a few hundred sets alone would
-// leave most of the 256 CUs idle).  The work is bound by the bytes of the
-// slave and master rows; W_I and re-read master rows come from the caches.
+// leave most of the 256 CUs idle).  The bytes of the slave and master rows would
+// take 5 us at p = 6, 216 sets, 64 columns; what the kernels spend is latency, so a
+// wavefront's row numbers are read together and its rows asked for together
+// (each row by itself: C 32, C^T 47 us; now 22 and 33).
+#include <type_traits>
+
 #include "mf_internal.h"
 
 namespace mf {
@@ -38,17 +41,49 @@ __device__ __forceinline__ void distribute_item(const ConstraintSet* __restrict_
   const int wave = __builtin_amdgcn_readfirstlane(tid / kCT);
   const int col = tile * kCT + lane;
   const bool ok = col < nvec;
-  for (int m = wave; m < cs.nm; m += kDistThreads / kCT) {
-    const int g = idx[cs.m0 + m];
-    xm[m * kCT + lane] = (ok && g >= 0) ? X[(int64_t)g * ld + col] : 0.0;
+  constexpr int kWaves = kDistThreads / kCT, kAhead = 8;
+  for (int mb = 0; mb < cs.nm; mb += kWaves * kAhead) {
+    int g[kAhead];
+    double v[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      g[u] = idx[cs.m0 + min(mb + wave + kWaves * u, cs.nm - 1)];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const bool in = ok && g[u] >= 0;
+      v[u] = X[(int64_t)(in ? g[u] : 0) * ld + (in ? col : 0)];
+      v[u] = in ? v[u] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int m = mb + wave + kWaves * u;
+      if (m < cs.nm) xm[m * kCT + lane] = v[u];
+    }
   }
   __syncthreads();
-  // W_I rows are wave-uniform: scalar loads, the LDS serves the master values
-  for (int s = sb + wave; s < se; s += kDistThreads / kCT) {
-    const double* w = W + cs.w0 + (int64_t)s * cs.nm;
-    double acc = 0.0;
-    for (int m = 0; m < cs.nm; ++m) acc = fma(w[m], xm[m * kCT + lane], acc);
-    if (ok) X[(int64_t)idx[cs.s0 + s] * ld + col] = acc;
+  // W_I rows are wave-uniform: scalar loads, the LDS serves the master values,
+  // each to the wavefront's slaves four at a time
+  constexpr int kRows = 4;
+  for (int s = sb + wave * kRows; s < se; s += kWaves * kRows) {
+    const double* w[kRows];
+    double acc[kRows];
+    int row[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      const int su = min(s + u, se - 1);
+      w[u] = W + cs.w0 + (int64_t)su * cs.nm;
+      row[u] = idx[cs.s0 + su];
+      acc[u] = 0.0;
+    }
+#pragma unroll 4
+    for (int m = 0; m < cs.nm; ++m) {
+      const double x = xm[m * kCT + lane];
+#pragma unroll
+      for (int u = 0; u < kRows; ++u) acc[u] = fma(w[u][m], x, acc[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      if (ok && s + u < se) X[(int64_t)row[u] * ld + col] = acc[u];
   }
 }
 
@@ -59,6 +94,9 @@ distribute_kernel(const ConstraintSet* __restrict__ sets, const int32_t* __restr
   distribute_item(sets, idx, W, X, ld, nvec, xm, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
+// NM: masters per wavefront (the last ones repeat the face's last master and are
+// dropped: a branch per product took longer than the product).
+template <int NM>
 __global__ void __launch_bounds__(kCondThreads)
 condense_kernel(const ConstraintSet* __restrict__ sets, const int32_t* __restrict__ idx,
                 const double* __restrict__ W, double* __restrict__ Y, int64_t ld, int nvec) {
@@ -73,40 +111,48 @@ condense_kernel(const ConstraintSet* __restrict__ sets, const int32_t* __restric
   const int col = blockIdx.y * kCT + lane;
   const bool ok = col < nvec;
   // each slave row belongs to exactly one set and one chunk: read it, then clear it
-  for (int s = wave; s < cnt; s += kCondWaves) {
-    double v = 0.0;
-    if (ok) {
-      const int64_t at = (int64_t)idx[cs.s0 + sb + s] * ld + col;
-      v = Y[at];
-      Y[at] = 0.0;
+  constexpr int kAhead = kCondSlaves / kCondWaves;
+  int row[kAhead];
+  double v[kAhead];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u)
+    row[u] = idx[cs.s0 + sb + min(wave + kCondWaves * u, cnt - 1)];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) v[u] = Y[(int64_t)row[u] * ld + (ok ? col : 0)];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    const int s = wave + kCondWaves * u;
+    if (s < cnt) {
+      ys[s * kCT + lane] = ok ? v[u] : 0.0;
+      if (ok) Y[(int64_t)row[u] * ld + col] = 0.0;
     }
-    ys[s * kCT + lane] = v;
   }
   const double* wsrc = W + cs.w0 + (int64_t)sb * cs.nm;
+  int master[NM], at[NM];
+#pragma unroll
+  for (int j = 0; j < NM; ++j) {
+    at[j] = min(wave + kCondWaves * j, cs.nm - 1);
+    master[j] = idx[cs.m0 + at[j]];
+  }
+#pragma unroll 8
   for (int i = tid; i < cnt * cs.nm; i += kCondThreads) wl[i] = wsrc[i];
   __syncthreads();
-  double acc[kMaxMPerWave];
+  double acc[NM];
 #pragma unroll
-  for (int j = 0; j < kMaxMPerWave; ++j) acc[j] = 0.0;
+  for (int j = 0; j < NM; ++j) acc[j] = 0.0;
+#pragma unroll 2
   for (int s = 0; s < cnt; ++s) {
-    const double v = ys[s * kCT + lane];
+    const double x = ys[s * kCT + lane];
     const double* w = wl + s * cs.nm;
 #pragma unroll
-    for (int j = 0; j < kMaxMPerWave; ++j) {
-      const int m = wave + kCondWaves * j;
-      if (m < cs.nm) acc[j] = fma(w[m], v, acc[j]);
-    }
+    for (int j = 0; j < NM; ++j) acc[j] = fma(w[at[j]], x, acc[j]);
   }
   if (!ok) return;
 #pragma unroll
-  for (int j = 0; j < kMaxMPerWave; ++j) {
-    const int m = wave + kCondWaves * j;
-    if (m < cs.nm) {
-      const int g = idx[cs.m0 + m];
-      // masters on a coarse edge belong to two sets, and every chunk adds its part
-      if (g >= 0) unsafeAtomicAdd(Y + (int64_t)g * ld + col, acc[j]);
-    }
-  }
+  for (int j = 0; j < NM; ++j)
+    // masters on a coarse edge belong to two sets, and every chunk adds its part
+    if (wave + kCondWaves * j < cs.nm && master[j] >= 0)
+      unsafeAtomicAdd(Y + (int64_t)master[j] * ld + col, acc[j]);
 }
 
 // kZeroRows rows per workgroup (a quarter per wavefront), one column per lane.
@@ -164,8 +210,16 @@ hipError_t launch_constraints_condense(const Operator& op, double* Y, int nvec, 
   if (op.max_masters > kCondWaves * kMaxMPerWave) return hipErrorInvalidValue;
   const dim3 grid((unsigned)op.nsets, (unsigned)((nvec + kCT - 1) / kCT),
                   (unsigned)((op.max_slaves + kCondSlaves - 1) / kCondSlaves));
-  hipLaunchKernelGGL(condense_kernel, grid, dim3(kCondThreads), 0, s, op.d_sets, op.d_cidx,
-                     op.d_cw, Y, ld, nvec);
+  auto go = [&](auto nm) {
+    hipLaunchKernelGGL((condense_kernel<decltype(nm)::value>), grid, dim3(kCondThreads), 0, s,
+                       op.d_sets, op.d_cidx, op.d_cw, Y, ld, nvec);
+  };
+  const int need = (op.max_masters + kCondWaves - 1) / kCondWaves;
+  if (need <= 2) go(std::integral_constant<int, 2>{});
+  else if (need <= 5) go(std::integral_constant<int, 5>{});
+  else if (need <= 8) go(std::integral_constant<int, 8>{});
+  else if (need <= 11) go(std::integral_constant<int, 11>{});
+  else go(std::integral_constant<int, kMaxMPerWave>{});
   return hipGetLastError();
 }
 
