@@ -67,6 +67,17 @@ int mf_cell_gather(mf_operator* op, int k, const double* R, int64_t ldr, const d
                    int64_t lde, int Fp, uint16_t* X0t, float* Tt, int64_t ldx, float* rho,
                    int pou_sqrt, const double* dscale, int blocked, void* stream);
 
+/* The linear branch of the network on every cell: Y(:, e k + j) := S x, x the
+ * cell's values of column j of R as mf_cell_gather forms them without rho
+ * (BF16), S Fp x Fp in BF16 (row-major, lds >= Fp, lds % 8 == 0), Y FP32 in
+ * the cell-blocked layout (block stride ldy >= Fp k).  k % 8 == 0.  X0 (ncells
+ * x Fp x k elements, 16-byte aligned) is a work array: where the batch is long
+ * the gather is part of the product and X0 is not touched.  Errors: MF_ERR_ARG,
+ * MF_ERR_UNSUPPORTED, MF_ERR_HIP. */
+int mf_cell_linear(mf_operator* op, int k, const double* R, int64_t ldr, int Fp,
+                   const uint16_t* S, int64_t lds, uint16_t* X0, float* Y, int64_t ldy,
+                   int pou_sqrt, const double* dscale, void* stream);
+
 /* Z := Z0 + sum_e Q_e^T W_e (rho * Yt): the partition-of-unity assembly of
  * the network outputs Yt (FP32, first F rows used, ldy >= ncells k) scaled
  * back by rho (1 when rho is NULL), with W_e the weights w_i (or sqrt(w_i)

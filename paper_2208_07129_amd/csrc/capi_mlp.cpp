@@ -67,6 +67,25 @@ int mf_cell_gather(mf_operator* handle, int k, const double* R, int64_t ldr, con
   return MF_OK;
 }
 
+int mf_cell_linear(mf_operator* handle, int k, const double* R, int64_t ldr, int Fp,
+                   const uint16_t* S, int64_t lds, uint16_t* X0, float* Y, int64_t ldy,
+                   int pou_sqrt, const double* dscale, void* stream) {
+  if (!handle || !R || !S || !X0 || !Y) return fail(MF_ERR_ARG, "operator, R, S, X0, Y non-NULL");
+  Operator* op = reinterpret_cast<Operator*>(handle);
+  if (op->refined) return fail(MF_ERR_UNSUPPORTED, "cell gather/scatter are built for uniform box meshes");
+  const int F = op->np * op->np * op->np;
+  if (k < 8 || k % 8 || ldr < k) return fail(MF_ERR_ARG, "need k a positive multiple of 8, ldr >= k");
+  if (Fp < F || Fp % 8) return fail(MF_ERR_ARG, "Fp must be >= np^3 and a multiple of 8");
+  if (lds < Fp || lds % 8 || !aligned16(S) || !aligned16(X0))
+    return fail(MF_ERR_ARG, "need lds >= Fp and a multiple of 8, S and X0 16-byte aligned");
+  if (ldy < (int64_t)Fp * k) return fail(MF_ERR_ARG, "ldy < Fp * k");
+  if (op->ncells * k >= ((int64_t)1 << 31)) return fail(MF_ERR_UNSUPPORTED, "batch too large");
+  hipError_t err = launch_cell_linear(*op, k, R, ldr, Fp, S, lds, X0, Y, ldy, pou_sqrt, dscale,
+                                      static_cast<hipStream_t>(stream));
+  if (err != hipSuccess) return hip_fail(err, "cell product launch");
+  return MF_OK;
+}
+
 int mf_cell_scatter(mf_operator* handle, int k, const float* Yt, int64_t ldy, const float* rho,
                     const double* diag, const double* R, int64_t ldr, double* Z, int64_t ldz,
                     int pou_sqrt, const double* dscale, int blocked, void* stream) {

@@ -349,6 +349,9 @@ hipError_t launch_cell_gather(const Operator& op, int k, const double* R, int64_
                               const double* E, int64_t lde, int Fp, uint16_t* X0t, float* Tt,
                               int64_t ldx, float* rho, int pou_sqrt, const double* dsc,
                               int blocked, hipStream_t s);
+hipError_t launch_cell_linear(const Operator& op, int k, const double* R, int64_t ldr, int Fp,
+                              const uint16_t* S, int64_t lds, uint16_t* X0, float* Y, int64_t ldy,
+                              int pou_sqrt, const double* dsc, hipStream_t s);
 hipError_t launch_cell_scatter(const Operator& op, int k, const float* Yt, int64_t ldy,
                                const float* rho, const double* diag, const double* R, int64_t ldr,
                                double* Z, int64_t ldz, int pou_sqrt, const double* dsc,

@@ -342,6 +342,40 @@ gemm_bf16_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
   }
 }
 
+// Partition-of-unity weight of a free node: 1 / (number of (cell, local
+// node) occurrences), per direction 2 on a shared cell face, 1 otherwise.
+__device__ inline double pou_weight(const GridDesc& g, int i1, int i2, int i3, int cx, int cy,
+                                    int cz) {
+  const int li[3] = {i1, i2, i3}, c[3] = {cx, cy, cz};
+  double w = 1.0;
+  for (int d = 0; d < 3; ++d) {
+    const bool periodic = g.N[d] == g.n[d] * g.p;
+    const bool lo = li[d] == 0, hi = li[d] == g.p;
+    if (!(lo || hi)) continue;
+    const bool outer = !periodic && ((lo && c[d] == 0) || (hi && c[d] == g.n[d] - 1));
+    if (!outer) w *= 0.5;
+  }
+  return w;
+}
+
+// The node number of a local node of cell (cx, cy, cz) (-1: constrained) and its
+// input factor sqrt(w)^[pou_sqrt] / sqrt(d) (d = dsc[node], 1 without dsc).
+__device__ inline int cell_node_factor(const GridDesc& g, int np, int cx, int cy, int cz, int i,
+                                       int pou_sqrt, const double* __restrict__ dsc, double& fin,
+                                       double* dhalf = nullptr) {
+  const int i1 = i % np, i2 = (i / np) % np, i3 = i / (np * np);
+  const int node = grid_node(g, cx, cy, cz, i1, i2, i3);
+  double dh = 1.0;
+  fin = 0.0;
+  if (node >= 0) {
+    const double ws = pou_sqrt ? sqrt(pou_weight(g, i1, i2, i3, cx, cy, cz)) : 1.0;
+    dh = dsc ? sqrt(dsc[node]) : 1.0;
+    fin = ws / dh;
+  }
+  if (dhalf) *dhalf = dh;
+  return node;
+}
+
 // The same product for op(B) = B (a long batch N), K <= 32 KS and no split.  A
 // wavefront keeps its 16 NB columns of B in registers for the whole K range and
 // the workgroup walks down M, 16 rows at a time, so B is read from memory once
@@ -356,13 +390,28 @@ gemm_bf16_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
 // The epilogue is a template parameter and its stores are dropped past the edge
 // by the buffer's bound: with a branch the count of stores in flight is unknown
 // and every step waited for the last one's (2.3 us a step).
-constexpr int kWideMaxM = 4096;  // rows of C, for the bias in LDS
+constexpr int kWideMaxM = 4096;   // rows of C, for the bias in LDS
+constexpr int kWideMinN = 32768;  // 128 columns on each of 256 CUs
 constexpr int wide_buffer(int ks, bool ta) { return ta ? 1024 : (ks * 64 + 255) / 256 * 256; }
 enum WideEpi { kWideF32, kWideF32Bias, kWideReluBf16, kWideMaskBf16 };
-template <int KS, int NB, bool TA, int EPI>
+//
+// CELLS: B is not read but formed, the scaled cell values of an FP64 multivector
+// (column e k + j of B: column j of cell e, row i its local node i, times the
+// node's factor, rounded to BF16 by way of FP32 as the cell gather does), so the
+// gathered block is neither written nor read (8000 cells, p = 6, 128 columns: with
+// the assembly 1848 -> 1662 us).
+struct WideCells {
+  GridDesc g;
+  int np, k, cells;  // cells: table entries per workgroup
+  const double* R;
+  int64_t ldr;
+  int pou_sqrt;
+  const double* dsc;
+};
+template <int KS, int NB, bool TA, int EPI, bool CELLS>
 __global__ void __launch_bounds__(256, 2)
 gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
-                 const uint16_t* __restrict__ B, int64_t ldb, GemmEpi ep) {
+                 const uint16_t* __restrict__ B, int64_t ldb, GemmEpi ep, WideCells wc) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   constexpr int kOob = (int)kGemmBuffer;
   extern __shared__ __attribute__((aligned(16))) char wide_sh[];
@@ -407,7 +456,63 @@ gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
   using WB = std::integral_constant<int, NB>;
   using W4 = std::integral_constant<int, 4>;
   u32x4 b[KS][NB];
-  {
+  if constexpr (CELLS) {
+    // node numbers and factors of the workgroup's cells, rows past F with factor 0
+    constexpr int RT = KS * 32;
+    double* sf = reinterpret_cast<double*>(sbias);
+    int* sn = reinterpret_cast<int*>(sf + wc.cells * RT);
+    const int ncells = wc.g.n[0] * wc.g.n[1] * wc.g.n[2];
+    const int e0 = (int)(lt * 64 * NB / wc.k);
+    for (int q = t; q < wc.cells * RT; q += 256) {
+      const int ce = q / RT, i = q - ce * RT, e = min(e0 + ce, ncells - 1);
+      double f;
+      int node = cell_node_factor(wc.g, wc.np, e % wc.g.n[0], e / wc.g.n[0] % wc.g.n[1],
+                                  e / (wc.g.n[0] * wc.g.n[1]), min(i, wc.np * wc.np * wc.np - 1),
+                                  wc.pou_sqrt, wc.dsc, f);
+      sf[q] = i < wc.np * wc.np * wc.np && node >= 0 ? f : 0.0;
+      sn[q] = node >= 0 ? node : 0;
+    }
+    __syncthreads();
+    const int64_t nl = nok ? n : 0;
+    const int e = nok ? (int)(nl / wc.k) : e0;
+    const double* Rj = wc.R + (nl - (int64_t)(nl / wc.k) * wc.k);
+    const int at = (e - e0) * RT + 8 * g;
+    // a step's rows are asked for while the step before is rounded and packed
+    double2 x[2][8][NB / 2];
+    auto ask = [&](int ks) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int w = 0; w < NB / 2; ++w)
+          x[ks & 1][i][w] = *reinterpret_cast<const double2*>(
+              Rj + (int64_t)sn[at + 32 * ks + i] * wc.ldr + 2 * w);
+    };
+    ask(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks + 1 < KS) ask(ks + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      uint32_t h[8][NB];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const double f = sf[at + 32 * ks + i];
+#pragma unroll
+        for (int w = 0; w < NB; ++w) {
+          const double y = w & 1 ? x[ks & 1][i][w / 2].y : x[ks & 1][i][w / 2].x;
+          h[i][w] = f32_to_bf16((float)(f != 0.0 ? y * f : 0.0));
+        }
+      }
+#pragma unroll
+      for (int w = 0; w < NB; ++w)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint32_t r = h[2 * i][w] | h[2 * i + 1][w] << 16;
+          asm volatile("" : "+v"(r));  // packed here, not where it is used
+          b[ks][w][i] = r;
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
     const int64_t rs = ep.kb > 0 ? ep.kb : ldb;
     const int64_t nc = n0 < N ? n0 : 0;  // past the end: nothing is read
     const int64_t b0 = ep.kb > 0 ? nc / ep.kb : 0;
@@ -545,22 +650,6 @@ gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
   }
 }
 
-// Partition-of-unity weight of a free node: 1 / (number of (cell, local
-// node) occurrences), per direction 2 on a shared cell face, 1 otherwise.
-__device__ inline double pou_weight(const GridDesc& g, int i1, int i2, int i3, int cx, int cy,
-                                    int cz) {
-  const int li[3] = {i1, i2, i3}, c[3] = {cx, cy, cz};
-  double w = 1.0;
-  for (int d = 0; d < 3; ++d) {
-    const bool periodic = g.N[d] == g.n[d] * g.p;
-    const bool lo = li[d] == 0, hi = li[d] == g.p;
-    if (!(lo || hi)) continue;
-    const bool outer = !periodic && ((lo && c[d] == 0) || (hi && c[d] == g.n[d] - 1));
-    if (!outer) w *= 0.5;
-  }
-  return w;
-}
-
 // One workgroup per (C cells, chunk of 64 columns); lane l of a wavefront: cell
 // l / k and column l % k of the C k <= 64 (cell, column) rows (C = 1: column l of
 // the chunk), wavefront ph: nodes i = ph, ph + 4, ...  rho = RMS of the cell's
@@ -575,25 +664,14 @@ __device__ inline double pou_weight(const GridDesc& g, int i1, int i2, int i3, i
 constexpr int kCols = 64;
 constexpr int kGatherNodeBytes = 2 * sizeof(double) + sizeof(int);  // LDS per (cell, node)
 
-// Per (cell, local node): the node number (-1 constrained), the input factor
-// sqrt(w)^[pou_sqrt] / sqrt(d) and sqrt(d) (d = dsc[node], 1 without dsc).
+// Per local node of a cell: the node number, the input factor and sqrt(d).
 __device__ inline void cell_node_factors(const GridDesc& g, int np, int cx, int cy, int cz,
                                          int pou_sqrt, const double* __restrict__ dsc, int* snode,
                                          double* sfin, double* sdh) {
   const int F = np * np * np;
-  for (int i = threadIdx.x; i < F; i += blockDim.x) {
-    const int i1 = i % np, i2 = (i / np) % np, i3 = i / (np * np);
-    const int node = grid_node(g, cx, cy, cz, i1, i2, i3);
-    double fi = 0.0, dh = 1.0;
-    if (node >= 0) {
-      const double ws = pou_sqrt ? sqrt(pou_weight(g, i1, i2, i3, cx, cy, cz)) : 1.0;
-      dh = dsc ? sqrt(dsc[node]) : 1.0;
-      fi = ws / dh;
-    }
-    snode[i] = node;
-    sfin[i] = fi;
-    if (sdh) sdh[i] = dh;
-  }
+  for (int i = threadIdx.x; i < F; i += blockDim.x)
+    snode[i] = cell_node_factor(g, np, cx, cy, cz, i, pou_sqrt, dsc, sfin[i],
+                                sdh ? sdh + i : nullptr);
 }
 
 template <bool MULTI>
@@ -1079,7 +1157,6 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   // (344 x 8000 x 344: 20 us with 64, 22 with 128; 31000 columns: 38 and 33; 344 x
   // 600 x 128000 in pieces: 181 and 148).  A split K range may be cut further to get there, in pieces of
   // at least 1024: each piece adds its tile once more.
-  constexpr int kWideMinN = 32768;  // 128 columns on each of 256 CUs
   constexpr int kFill = 512, kMinPiece = 1024;
   if (split && tiles_of(128) * kz < kFill && K > kMinPiece) {
     const int64_t want = (kFill + tiles_of(128) - 1) / tiles_of(128);
@@ -1124,8 +1201,8 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
       const dim3 wgrid((unsigned)((wgs + kXcds - 1) / kXcds * kXcds));
       const size_t lds = 2 * 16 * wide_buffer(KS, TA) + ((size_t)M + 15) / 16 * 64;  // <= 56 KiB
       auto run = [&](auto ec) {
-        hipLaunchKernelGGL((gemm_wide_kernel<KS, NB, TA, decltype(ec)::value>), wgrid, dim3(256),
-                           lds, s, M, N, K, A, lda, B, ldb, ep);
+        hipLaunchKernelGGL((gemm_wide_kernel<KS, NB, TA, decltype(ec)::value, false>), wgrid,
+                           dim3(256), lds, s, M, N, K, A, lda, B, ldb, ep, WideCells{});
       };
       if constexpr (TA) run(std::integral_constant<int, kWideMaskBf16>{});
       else if (epi == kWideF32) run(std::integral_constant<int, kWideF32>{});
@@ -1160,6 +1237,49 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   if (far) form(std::integral_constant<int, 64>{}, std::true_type{});
   else if (big) form(std::integral_constant<int, 128>{}, std::false_type{});
   else form(std::integral_constant<int, 64>{}, std::false_type{});
+  return hipGetLastError();
+}
+
+// Y = S X0 cell by cell, X0 the gathered block (not normalised), in the cell-blocked
+// layout (block stride ldy).  Fused where the batch is long, a cell's rows fit the
+// one-pass kernel and a workgroup's cells their table, else the gather
+// into X0 and the product.  With the assembly, gather and product against this:
+// p = 6, 12^3 cells, 24 columns 120 / 103 us, 64 225 / 189, 256 825 / 740; p = 4, 14^3,
+// 16 66 / 56, 64 110 / 86; p = 2, 24^3, 8 78 / 71, 128 271 / 244.
+hipError_t launch_cell_linear(const Operator& op, int k, const double* R, int64_t ldr, int Fp,
+                              const uint16_t* S, int64_t lds, uint16_t* X0, float* Y, int64_t ldy,
+                              int pou_sqrt, const double* dsc, hipStream_t s) {
+  const int64_t n = op.ncells * k;
+  const int ks = Fp <= 128 ? 4 : Fp <= 256 ? 8 : 11;
+  constexpr int NB = 2, kCols = 64 * NB;
+  const int cells = kCols % k == 0 ? kCols / k : k % kCols == 0 ? 1 : (kCols - 1) / k + 2;
+  const size_t table = (size_t)cells * ks * 32 * (sizeof(double) + sizeof(int));
+  const bool aligned = ldr % 2 == 0 && reinterpret_cast<uintptr_t>(R) % 16 == 0 &&
+                       reinterpret_cast<uintptr_t>(Y) % 16 == 0 && ldy % 4 == 0;
+  const int64_t far = 4 * (16 * (int64_t)k + (kCols / k + 2) * ldy + 16 * lds + Fp);
+  GemmEpi ep{};
+  ep.out_f32 = Y;
+  ep.ld_f32 = ldy;
+  ep.kb = k;
+  if (k % 8 || n < kWideMinN || Fp > 352 || table > 32 * 1024 || !aligned ||
+      far >= (int64_t)1 << 31) {
+    hipError_t err = launch_cell_gather(op, k, R, ldr, nullptr, 0, Fp, X0, nullptr,
+                                        (int64_t)Fp * k, nullptr, pou_sqrt, dsc, 1, s);
+    if (err != hipSuccess) return err;
+    return launch_gemm_bf16(Fp, (int)n, Fp, false, false, S, lds, X0, (int64_t)Fp * k, 0, ep, s);
+  }
+  const WideCells wc{op.grid, op.np, k, cells, R, ldr, pou_sqrt, dsc};
+  const int64_t wgs = (n + kCols - 1) / kCols;
+  const dim3 grid((unsigned)((wgs + kXcds - 1) / kXcds * kXcds));
+  auto go = [&](auto ksc) {
+    constexpr int KS = decltype(ksc)::value;
+    hipLaunchKernelGGL((gemm_wide_kernel<KS, NB, false, kWideF32, true>), grid, dim3(256),
+                       2 * 16 * wide_buffer(KS, false) + table, s, Fp, (int)n, Fp, S, lds, nullptr,
+                       (int64_t)0, ep, wc);
+  };
+  if (ks == 4) go(std::integral_constant<int, 4>{});
+  else if (ks == 8) go(std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, 11>{});
   return hipGetLastError();
 }
 

@@ -41,8 +41,8 @@ EXPORTS = ("mf_num_dofs", "mf_num_cells", "mf_quad_points", "mf_constrained_mask
            "mf_axpby",
            "mf_jacobi", "mf_spd_solve",
            # include/mfmlp.h
-           "mf_mlp_gemm", "mf_cell_gather", "mf_cell_scatter", "mf_mse_grad", "mf_row_sums",
-           "mf_adam", "mf_symmetrize", "mf_to_bf16", "mf_fill_f32", "mf_skip_floor",
+           "mf_mlp_gemm", "mf_cell_gather", "mf_cell_linear", "mf_cell_scatter", "mf_mse_grad",
+           "mf_row_sums", "mf_adam", "mf_symmetrize", "mf_to_bf16", "mf_fill_f32", "mf_skip_floor",
            "mf_skip_floor_work",
            # include/mfcheb.h
            "mf_gll_mass", "mf_cheb_step", "mf_sym_eig", "mf_sym_eig_work",
@@ -129,6 +129,7 @@ def lib() -> ctypes.CDLL:
             "mf_mlp_gemm": (I, [I, I, I, I, I, P, I64, P, I64, I, P, I, P, I64, P, I64, I, P, I64,
                                 I, P]),
             "mf_cell_gather": (I, [P, I, P, I64, P, I64, I, P, P, I64, P, I, P, I, P]),
+            "mf_cell_linear": (I, [P, I, P, I64, I, P, I64, P, P, I64, I, P, P]),
             "mf_cell_scatter": (I, [P, I, P, I64, P, P, P, I64, P, I64, I, P, I, P]),
             "mf_symmetrize": (I, [I, P, I64, P, P]),
             "mf_skip_floor": (I, [I, P, I64, P, I64, D, P, I64, P, P]),

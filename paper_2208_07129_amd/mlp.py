@@ -272,13 +272,18 @@ class CellMLP:
         and assembly stream whole cells."""
         k = R.shape[1]
         blocked = linear and k % 8 == 0
-        b = self.gather(R, pou_sqrt=True, normalise=not linear, blocked=blocked)
         Fp, H = self.Fp, self.H
+        b = self._buffers(k) if blocked else self.gather(R, pou_sqrt=True, normalise=not linear)
         ld = Fp * k if blocked else b["ld"]
-        if linear:
-            n = b["ld"] if not blocked else self.op.ncells * k
-            self._gemm(Fp, n, Fp, False, False, self.wbf[4][:, H:], H + Fp, b["X0"], ld,
-                       out_f32=b["Y"], ld_f32=ld, kb=k if blocked else 0)
+        if blocked:
+            _check(lib().mf_cell_linear(self.op._h, k, R.data_ptr(), R.stride(0), Fp,
+                                        self.wbf[4][:, H:].data_ptr(), H + Fp, b["X0"].data_ptr(),
+                                        b["Y"].data_ptr(), ld, 1,
+                                        None if self.dscale is None else self.dscale.data_ptr(),
+                                        _stream_ptr(None)))
+        elif linear:
+            self._gemm(Fp, ld, Fp, False, False, self.wbf[4][:, H:], H + Fp, b["X0"], ld,
+                       out_f32=b["Y"], ld_f32=ld)
         else:
             self.forward(b)
         _check(lib().mf_cell_scatter(self.op._h, k, b["Y"].data_ptr(), ld,
