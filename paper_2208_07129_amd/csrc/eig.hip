@@ -133,62 +133,51 @@ bj_norm_kernel(int K, const double* __restrict__ Aw, double* __restrict__ part, 
 // A serial chain of 63 rounds on one CU: what counts is the length of a round.
 // The 64 indices sit in 32 slot pairs (position t above position 63 - t) and
 // move one position per round, so every round reads and writes the same places:
-// the 2 x 2 block of slot pairs (i < j) takes the row rotation of pair i and the
+// the 2 x 2 block of slot pairs (i, j) takes the row rotation of pair i and the
 // column rotation of pair j at once and is stored at its place of the next
-// round (two LDS copies; four planes [slot][slot] of 32 x 32, of which the blocks
-// i < j are kept up: the matrix is symmetric).  The 13 wavefronts work side by
-// side with one barrier per round: wavefront 0 has the diagonal blocks in
-// registers and forms the next round's angles, for which it takes the two
-// elements that meet through this round's rotations by itself; eight rotate the
-// off-diagonal blocks, one per lane; four hold the rotation V in registers (lane =
-// row, a wavefront = eight slot pairs) and pass two columns each to their
-// neighbours.  The angle needs two chains of reciprocal square roots.  155 us a
-// launch with division, separate row and column passes and three barriers; 63
-// with the angles, the blocks and V one after the other; 35 so.
+// round (two LDS copies of four planes [slot][slot] of 32 x 33).  The 13
+// wavefronts work side by side with one barrier per round: wavefront 0 has the
+// diagonal blocks in registers and forms the next round's angles, for which it
+// takes the elements that meet through this round's rotations by itself; eight
+// rotate the off-diagonal blocks, (i, j) and (j, i) per lane; four hold the
+// rotation V in registers (lane = row, a wavefront = eight slot pairs) and pass
+// two columns each to their neighbours.  155 us a launch with separate row and
+// column passes and three barriers, 64 so.
+//
+// The arithmetic is that of the plain cyclic sweep, element by element: rows, then
+// columns, p the smaller index of a pair, ap' = fma(c, ap, -(s aq)) and aq' =
+// fma(s, ap, c aq), nothing taken from symmetry.  Jacobi's path is sensitive enough
+// to roundings that other orders, or a shorter formula for the angle (two reciprocal
+// square roots, 35 us a launch with half of the blocks), end with the signs of some
+// eigenvectors changed; the same holds for the order of the update's sums.
 constexpr int kBjP2 = kBjPair / 2;  // slot pairs
-constexpr int kBjPlane = kBjP2 * kBjP2;
+constexpr int kBjRow = kBjP2 + 1, kBjPlane = kBjP2 * kBjRow;
 constexpr int kBjAWaves = 8, kBjVWaves = 4;  // wavefronts on the blocks, on V
 constexpr int kBjSweepThreads = 64 * (1 + kBjAWaves + kBjVWaves);
 constexpr size_t kBjSweepLds = 2 * 4 * (size_t)kBjPlane * sizeof(double);
-static_assert(kBjP2 * (kBjP2 - 1) / 2 <= 64 * kBjAWaves, "one off-diagonal block per lane");
+static_assert(kBjP2 * (kBjP2 - 1) / 2 <= 64 * kBjAWaves, "two off-diagonal blocks per lane");
 static_assert(2 * 4 * kBjPlane >= kBjPair * kBjLd, "V is written out through the blocks' LDS");
 
-// x^{-1/2} for x in [1/8, 4]: the hardware estimate and two Newton steps.
-__device__ __forceinline__ double rsqrt_unit(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int n = 0; n < 2; ++n) {
-    const double e = fma(-x * y, y, 1.0);
-    y = fma(0.5 * y, e, y);
-  }
-  return y;
-}
-
-// The rotation that zeroes apq, |angle| <= pi/4: with d = aqq - app and
-// b = 2 apq, cos 2t = |d| / sqrt(d^2 + b^2) and sin 2t = sign(d) b / sqrt(d^2 + b^2)
-// (d = 0: the positive angle); d and b are scaled by a power of two first.
+// The rotation that zeroes apq, |angle| <= pi/4.
 __device__ __forceinline__ void jacobi_angle(double app, double aqq, double apq, double& c,
                                              double& s) {
   c = 1.0;
   s = 0.0;
-  if (!(fabs(apq) > 1e-300)) return;
-  double d = aqq - app, b = 2.0 * apq;
-  const double m = fmax(fabs(d), fabs(b));
-  if (!(m < 1.7e308)) {  // infinite or not a number: as the quotient form would have it
-    const double th = d / b, at = fabs(th);
-    const double tn = (th >= 0.0 ? 1.0 : -1.0) / (at + sqrt(th * th + 1.0));
-    c = 1.0 / sqrt(tn * tn + 1.0);
+  if (fabs(apq) > 1e-300) {
+    const double th = (aqq - app) / (2.0 * apq);
+    const double at = fabs(th);
+    const double tn =
+        (th >= 0.0 ? 1.0 : -1.0) / (at + (at < 1e150 ? sqrt(fma(th, th, 1.0)) : at));
+    c = 1.0 / sqrt(fma(tn, tn, 1.0));
     s = tn * c;
-    return;
   }
-  const int ex = -__builtin_amdgcn_frexp_exp(m);
-  d = __builtin_amdgcn_ldexp(d, ex);
-  b = __builtin_amdgcn_ldexp(b, ex);
-  const double rh = rsqrt_unit(fma(d, d, b * b));
-  const double c2 = fma(0.5 * fabs(d), rh, 0.5);
-  const double rc = rsqrt_unit(c2);
-  c = c2 * rc;
-  s = (d == 0.0 ? 0.5 * fabs(b) : (d < 0.0 ? -0.5 : 0.5) * b) * rh * rc;
+}
+// The rotated pair (p, q).
+__device__ __forceinline__ double rot_p(double c, double s, double p, double q) {
+  return fma(c, p, -(s * q));
+}
+__device__ __forceinline__ double rot_q(double c, double s, double p, double q) {
+  return fma(s, p, c * q);
 }
 
 // Where the member of slot pair pr in slot (0 above, 1 below) goes next round.
@@ -201,6 +190,13 @@ __device__ __forceinline__ void bj_next(int slot, int pr, int& ns, int& np) {
     np = pr < kBjP2 - 1 ? pr + 1 : kBjP2 - 1;
   }
 }
+// The place next round of element (member u of pair pi, member w of pair pj).
+__device__ __forceinline__ int bj_place(int u, int pi, int w, int pj) {
+  int is, ip, js, jp;
+  bj_next(u, pi, is, ip);
+  bj_next(w, pj, js, jp);
+  return (is * 2 + js) * kBjPlane + ip * kBjRow + jp;
+}
 
 __global__ void __launch_bounds__(kBjSweepThreads)
 bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__ J,
@@ -208,9 +204,10 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
   if (st->done != 0.0) return;
   extern __shared__ double sh[];
   double* a = sh;  // 2 copies of 4 planes
-  __shared__ double2 cs[2][kBjP2];
-  __shared__ double dg[2][2][kBjP2];              // rotated diagonal, [round][slot][pair]
-  __shared__ double xch[2][kBjVWaves][2][64];     // V's columns on their way to a neighbour
+  constexpr int kCopy = 4 * kBjPlane;
+  __shared__ double2 cs[2][kBjP2];             // (c, s); -c where the lower member is p
+  __shared__ double dg[2][2][kBjP2];           // rotated diagonal, [round][slot][pair]
+  __shared__ double xch[2][kBjVWaves][2][64];  // V's columns on their way to a neighbour
   const int t = threadIdx.x, nb = K / kBj, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   constexpr int kRounds = kBjPair - 1;
@@ -220,96 +217,117 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
     const int row = i / kBjPair, col = i % kBjPair;
     const int si = row >= kBjP2, sj = col >= kBjP2;
     const int pi = si ? kBjPair - 1 - row : row, pj = sj ? kBjPair - 1 - col : col;
-    a[(si * 2 + sj) * kBjPlane + pi * kBjP2 + pj] =
+    a[(si * 2 + sj) * kBjPlane + pi * kBjRow + pj] =
         Aw[(int64_t)pair_index(P, Q, row) * K + pair_index(P, Q, col)];
   }
   __syncthreads();
   if (wave == 0) {
-    const int p = lane & (kBjP2 - 1);
-    double d0 = a[p * (kBjP2 + 1)], d1 = a[3 * kBjPlane + p * (kBjP2 + 1)];
-    double x = a[kBjPlane + p * (kBjP2 + 1)], c, s;
-    // items at the two positions; the angle is that of the smaller one first
-    int i0 = p == 0 ? 0 : p, i1 = kBjPair - 1 - p;
+    __builtin_amdgcn_s_setprio(3);  // the chain that every round waits for
+    const int p = lane & (kBjP2 - 1), dia = p * kBjRow + p;
+    // the pair's block, [slot][slot]
+    double dtt = a[dia], dtb = a[kBjPlane + dia], dbt = a[2 * kBjPlane + dia],
+           dbb = a[3 * kBjPlane + dia], c, s;
+    int i0 = p, i1 = kBjPair - 1 - p;  // the items at the two positions
     auto angle = [&]() {
       const bool up = i0 < i1;
-      jacobi_angle(up ? d0 : d1, up ? d1 : d0, x, c, s);
-      s = up ? s : -s;
+      jacobi_angle(up ? dtt : dbb, up ? dbb : dtt, up ? dtb : dbt, c, s);
     };
     angle();
-    if (lane < kBjP2) cs[0][p] = make_double2(c, s);
+    if (lane < kBjP2) cs[0][p] = make_double2(i0 < i1 ? c : -c, s);
     __syncthreads();
     // the members of slot pair p next round sit in (u, pu) and (w, pw) now
     const int u = p == kBjP2 - 1 ? 1 : 0, pu = p == kBjP2 - 1 ? p : (p == 0 ? 0 : p + 1);
     const int w = p == 0 ? 0 : 1, pw = p == 0 ? 1 : p - 1;
-    const bool sw = pu > pw;  // the blocks above the diagonal are kept
-    const int lo = sw ? pw : pu, hi = sw ? pu : pw;
-    const int m01 = sw ? 2 : 1, m10 = 3 - m01;  // plane of (slot of pu, slot of pw)
-    const double* blk = a + lo * kBjP2 + hi;
-    // the pair's own off-diagonal element, 0 now, goes to a block of the next round
-    int is, ip, js, jp;
-    bj_next(0, p, is, ip);
-    bj_next(1, p, js, jp);
-    double* zero = a + (is * 2 + js) * kBjPlane + ip * kBjP2 + jp;  // ip < jp
+    const int to_tb = bj_place(0, p, 1, p), to_bt = bj_place(1, p, 0, p);
     for (int rr = 0; rr + 1 < kRounds; ++rr) {
-      const double* ac = blk + (rr & 1) * 4 * kBjPlane;
-      const double m00 = ac[0], v01 = ac[m01 * kBjPlane], v10 = ac[m10 * kBjPlane],
-                   m11 = ac[3 * kBjPlane];
+      const double* ac = a + (rr & 1) * kCopy;
+      double* an = a + ((rr + 1) & 1) * kCopy;
       const double2 ru = cs[rr & 1][pu], rw = cs[rr & 1][pw];
-      // this round's rotation of the diagonal, handed on to the next places
-      const double cx = c * x, sx = s * x;
-      const double y0 = c * d0 - sx, y1 = s * d0 + cx;  // rows, first column
-      const double z0 = cx - s * d1, z1 = sx + c * d1;  // rows, second column
-      if (lane < kBjP2) {
-        dg[rr & 1][0][p] = c * y0 - s * z0;
-        dg[rr & 1][1][p] = s * y1 + c * z1;
-        zero[((rr + 1) & 1) * 4 * kBjPlane] = 0.0;
+      const double cu = fabs(ru.x), su = ru.y, cw = fabs(rw.x), sw = rw.y;
+      const int fu = __double2hiint(ru.x) < 0, fw = __double2hiint(rw.x) < 0;  // slot of p
+      // element (member m of pair x, member n of pair y) after this round
+      auto meet = [&](int x, int m, int fx, double cx, double sx, int y, int n, int fy, double cy,
+                      double sy) {
+        const double* e = ac + x * kBjRow + y;
+        const double pp = e[(fx * 2 + fy) * kBjPlane], pq = e[(fx * 2 + 1 - fy) * kBjPlane];
+        const double qp = e[((1 - fx) * 2 + fy) * kBjPlane],
+                     qq = e[((1 - fx) * 2 + 1 - fy) * kBjPlane];
+        const bool rp = m == fx, cp = n == fy;
+        const double ra = rp ? cx : sx, rb = rp ? -sx : cx;
+        const double ca = cp ? cy : sy, cb = cp ? -sy : cy;
+        const double yp = fma(ra, pp, rb * qp), yq = fma(ra, pq, rb * qq);
+        return fma(ca, yp, cb * yq);
+      };
+      const double ntb = meet(pu, u, fu, cu, su, pw, w, fw, cw, sw);
+      const double nbt = meet(pw, w, fw, cw, sw, pu, u, fu, cu, su);
+      // this round's rotation of the pair's own block, handed on to the next places
+      {
+        const bool up = i0 < i1;
+        const double pp = up ? dtt : dbb, pq = up ? dtb : dbt, qp = up ? dbt : dtb,
+                     qq = up ? dbb : dtt;
+        const double yp = rot_p(c, s, pp, qp), yq = rot_p(c, s, pq, qq);
+        const double zp = rot_q(c, s, pp, qp), zq = rot_q(c, s, pq, qq);
+        const double npp = rot_p(c, s, yp, yq), npq = rot_q(c, s, yp, yq);
+        const double nqp = rot_p(c, s, zp, zq), nqq = rot_q(c, s, zp, zq);
+        if (lane < kBjP2) {
+          dg[rr & 1][0][p] = up ? npp : nqq;
+          dg[rr & 1][1][p] = up ? nqq : npp;
+          an[to_tb] = up ? npq : nqp;
+          an[to_bt] = up ? nqp : npq;
+        }
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      const double a0 = u ? ru.y : ru.x, a1 = u ? ru.x : -ru.y;
-      const double b0 = w ? rw.y : rw.x, b1 = w ? rw.x : -rw.y;
-      const double e0 = fma(a0, m00, a1 * v10), e1 = fma(a0, v01, a1 * m11);
-      x = fma(b0, e0, b1 * e1);
-      d0 = dg[rr & 1][u][pu];
-      d1 = dg[rr & 1][w][pw];
+      dtt = dg[rr & 1][u][pu];
+      dbb = dg[rr & 1][w][pw];
+      dtb = ntb;
+      dbt = nbt;
       i0 = p == 0 ? 0 : (i0 == kRounds ? 1 : i0 + 1);
       i1 = i1 == kRounds ? 1 : i1 + 1;
       angle();
-      if (lane < kBjP2) cs[(rr + 1) & 1][p] = make_double2(c, s);
+      if (lane < kBjP2) cs[(rr + 1) & 1][p] = make_double2(i0 < i1 ? c : -c, s);
       __syncthreads();
     }
     __syncthreads();
     __syncthreads();
   } else if (wave <= kBjAWaves) {
-    // off-diagonal block (pi, pj): rows r and 30 - r of the triangle fill 32 lanes
+    // off-diagonal blocks (pi, pj) and (pj, pi), pi < pj: rows fr and 30 - fr of the
+    // triangle fill 32 lanes
     const int e = t - 64, fr = e / kBjP2, fk = e % kBjP2;
     const bool upper = fk < kBjP2 - 1 - fr;
     const int pi = upper ? fr : kBjP2 - 2 - fr, pj = upper ? fr + 1 + fk : fk;
     const bool on = fr < kBjP2 / 2 - 1 || upper;
-    int to[2][2];
+    int to[2][2][2];  // [block][member][member]
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        int is, ip, js, jp;
-        bj_next(u, pi, is, ip);
-        bj_next(w, pj, js, jp);
-        to[u][w] = ip <= jp ? (is * 2 + js) * kBjPlane + ip * kBjP2 + jp
-                            : (js * 2 + is) * kBjPlane + jp * kBjP2 + ip;
+      for (int n = 0; n < 2; ++n) {
+        to[0][m][n] = bj_place(m, pi, n, pj);
+        to[1][m][n] = bj_place(m, pj, n, pi);
       }
     __syncthreads();
     for (int rr = 0; rr + 1 < kRounds; ++rr) {
-      const double* ac = a + (rr & 1) * 4 * kBjPlane + pi * kBjP2 + pj;
-      double* an = a + ((rr + 1) & 1) * 4 * kBjPlane;
+      const double* ac = a + (rr & 1) * kCopy;
+      double* an = a + ((rr + 1) & 1) * kCopy;
       if (on) {
-        const double2 ri = cs[rr & 1][pi], rj = cs[rr & 1][pj];
-        const double tt = ac[0], tb = ac[kBjPlane], bt = ac[2 * kBjPlane], bb = ac[3 * kBjPlane];
-        // rows: (top, bottom) <- (c top - s bottom, s top + c bottom), then columns
-        const double x0 = ri.x * tt - ri.y * bt, y0 = ri.x * tb - ri.y * bb;
-        const double x1 = ri.y * tt + ri.x * bt, y1 = ri.y * tb + ri.x * bb;
-        an[to[0][0]] = rj.x * x0 - rj.y * y0;
-        an[to[0][1]] = rj.y * x0 + rj.x * y0;
-        an[to[1][0]] = rj.x * x1 - rj.y * y1;
-        an[to[1][1]] = rj.y * x1 + rj.x * y1;
+        const double2 r0 = cs[rr & 1][pi], r1 = cs[rr & 1][pj];
+        const int f0 = __double2hiint(r0.x) < 0, f1 = __double2hiint(r1.x) < 0;
+        auto block = [&](int x, int y, int fx, int fy, double cx, double sx, double cy, double sy,
+                         const int (&dst)[2][2]) {
+          const double* b = ac + x * kBjRow + y;
+          const int px = fx * 2 * kBjPlane, qx = 2 * kBjPlane - px, py = fy * kBjPlane,
+                    qy = kBjPlane - py;
+          const double pp = b[px + py], pq = b[px + qy], qp = b[qx + py], qq = b[qx + qy];
+          const double yp = rot_p(cx, sx, pp, qp), yq = rot_p(cx, sx, pq, qq);
+          const double zp = rot_q(cx, sx, pp, qp), zq = rot_q(cx, sx, pq, qq);
+          const int d0p = fy ? dst[0][1] : dst[0][0], d0q = fy ? dst[0][0] : dst[0][1];
+          const int d1p = fy ? dst[1][1] : dst[1][0], d1q = fy ? dst[1][0] : dst[1][1];
+          an[fx ? d1p : d0p] = rot_p(cy, sy, yp, yq);
+          an[fx ? d1q : d0q] = rot_q(cy, sy, yp, yq);
+          an[fx ? d0p : d1p] = rot_p(cy, sy, zp, zq);
+          an[fx ? d0q : d1q] = rot_q(cy, sy, zp, zq);
+        };
+        block(pi, pj, f0, f1, fabs(r0.x), r0.y, fabs(r1.x), r1.y, to[0]);
+        block(pj, pi, f1, f0, fabs(r1.x), r1.y, fabs(r0.x), r0.y, to[1]);
       }
       __syncthreads();
     }
@@ -328,10 +346,13 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
     for (int rr = 0; rr < kRounds; ++rr) {
 #pragma unroll
       for (int k = 0; k < G; ++k) {
-        const double2 q = cs[rr & 1][G * g + k];
-        const double x = top[k], y = bot[k];
-        top[k] = q.x * x - q.y * y;
-        bot[k] = q.y * x + q.x * y;
+        const double2 q2 = cs[rr & 1][G * g + k];
+        const double c = fabs(q2.x), s = q2.y;
+        const bool up = __double2hiint(q2.x) >= 0;
+        const double x = up ? top[k] : bot[k], y = up ? bot[k] : top[k];
+        const double xr = rot_p(c, s, x, y), yr = rot_q(c, s, x, y);
+        top[k] = up ? xr : yr;
+        bot[k] = up ? yr : xr;
       }
       xch[rr & 1][g][0][lane] = top[0];
       xch[rr & 1][g][1][lane] = bot[G - 1];
@@ -369,22 +390,15 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
 // of pair j, replaced by J_i^T piece J_j.  Workgroups [np^2, np^2 + np K/64):
 // rows 64 rb .. 64 rb + 63 of V in the columns of pair j, replaced by
 // piece J_j.  The pieces are disjoint, so the update is in place.
-//
-// Matrix cores (v_mfma_f64_16x16x4f64: A[i][c] in lane i + 16 c, B[c][j] in lane
-// j + 16 c, D[i][j] in lane j + 16 (i mod 4), register i / 4).  A wavefront forms
-// 16 columns of the result: first of piece J_j, whose registers are then the
-// operand B of J_i^T times it, so nothing but the piece (transposed) and the
-// rotations passes through LDS.  Bound by the two products at the matrix cores'
-// rate on as many CUs as there are pieces: K = 256, 24 us with 256 threads on the
-// vector ALUs (6 bytes of LDS per multiply-add), 16.5 with 512, 14.8 so.
-constexpr int kBjUpdThreads = 256;
-typedef double v4d __attribute__((ext_vector_type(4)));
+// Bound by the LDS reads of the products (6 bytes per multiply-add); 512 threads
+// instead of 256 hide more of the loads: 24 -> 16.5 us at K = 256.
+constexpr int kBjUpdThreads = 512;
 __global__ void __launch_bounds__(kBjUpdThreads)
 bj_update_kernel(int K, int r, double* __restrict__ Aw, double* __restrict__ Vw,
                  const double* __restrict__ J, const BjState* __restrict__ st) {
   if (st->done != 0.0) return;
   extern __shared__ double sh[];
-  double* Bt = sh;                      // the piece, transposed
+  double* B = sh;                       // the piece (then J_i^T piece)
   double* Ji = sh + kBjPair * kBjLd;
   double* Jj = sh + 2 * kBjPair * kBjLd;
   const int t = threadIdx.x, nb = K / kBj, np = nb / 2;
@@ -410,47 +424,60 @@ bj_update_kernel(int K, int r, double* __restrict__ Aw, double* __restrict__ Vw,
     const int e = e0 + t;
     const int row = e / kBjPair, col = e % kBjPair;
     const int grow = on_a ? pair_index(Pi, Qi, row) : rb * kBjPair + row;
-    Bt[col * kBjLd + row] = base[(int64_t)grow * K + pair_index(Pj, Qj, col)];
+    B[row * kBjLd + col] = base[(int64_t)grow * K + pair_index(Pj, Qj, col)];
     Jj[row * kBjLd + col] = jj[e];
     if (on_a) Ji[row * kBjLd + col] = ji[e];
   }
   __syncthreads();
-  const int lane = t & 63, l16 = lane & 15, c4 = lane >> 4, n0 = (t >> 6) * 16;
-  // M^T (16 columns of N): tile m of rows, operands M[b][row], N[b][column]
-  v4d p[4];
+  // thread (ty, tx): rows ty + 32 u, columns tx + 16 w of the 64 x 64 result
+  const int ty = t / 16, tx = t % 16;
+  double acc[2][4];
+  if (on_a) {  // B := J_i^T B
 #pragma unroll
-  for (int m = 0; m < 4; ++m) p[m] = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int b = 0; b < kBjPair; b += 4) {
-    const double y = Jj[(b + c4) * kBjLd + n0 + l16];
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-      p[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Bt[(b + c4) * kBjLd + 16 * m + l16], y, p[m], 0,
-                                                  0, 0);
-  }
-  if (on_a) {
-    v4d q[4];
+      for (int w = 0; w < 4; ++w) acc[u][w] = 0.0;
+    for (int b = 0; b < kBjPair; ++b) {
+      double x[2], y[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) q[m] = v4d{0.0, 0.0, 0.0, 0.0};
+      for (int u = 0; u < 2; ++u) x[u] = Ji[b * kBjLd + ty + 32 * u];
 #pragma unroll
-    for (int b = 0; b < kBjPair; b += 4) {  // rows b .. b + 3 of the first product
-      const double y = p[b / 16][(b / 4) % 4];
+      for (int w = 0; w < 4; ++w) y[w] = B[b * kBjLd + tx + 16 * w];
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
-        q[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ji[(b + c4) * kBjLd + 16 * m + l16], y, q[m],
-                                                    0, 0, 0);
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) acc[u][w] = fma(x[u], y[w], acc[u][w]);
     }
+    __syncthreads();
 #pragma unroll
-    for (int m = 0; m < 4; ++m) p[m] = q[m];
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) B[(ty + 32 * u) * kBjLd + tx + 16 * w] = acc[u][w];
+    __syncthreads();
   }
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int row = 16 * m + 4 * u + c4;
-      const int grow = on_a ? pair_index(Pi, Qi, row) : rb * kBjPair + row;
-      base[(int64_t)grow * K + pair_index(Pj, Qj, n0 + l16)] = p[m][u];
-    }
+    for (int w = 0; w < 4; ++w) acc[u][w] = 0.0;
+  for (int b = 0; b < kBjPair; ++b) {  // B J_j
+    double x[2], y[4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) x[u] = B[(ty + 32 * u) * kBjLd + b];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) y[w] = Jj[b * kBjLd + tx + 16 * w];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) acc[u][w] = fma(x[u], y[w], acc[u][w]);
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int row = ty + 32 * u;
+    const int grow = on_a ? pair_index(Pi, Qi, row) : rb * kBjPair + row;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      base[(int64_t)grow * K + pair_index(Pj, Qj, tx + 16 * w)] = acc[u][w];
+  }
 }
 
 // Eigenvalues ascending by rank (ties by index), eigenvector columns moved to
