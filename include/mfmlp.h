@@ -126,6 +126,17 @@ int64_t mf_skip_floor_work(int F);
 int mf_mse_grad(int F, int Fp, int64_t N, const float* Yt, const float* Tt, int64_t ld,
                 const float* roww, float scale, uint16_t* dYt, double* loss, void* stream);
 
+/* The last layer and its loss gradient in one call: y = A B + bias (A Fp x K,
+ * lda; B K x N, ld), dYt = 2 scale w[n] (y - Tt) for features < F (0 for the
+ * padding features and for rows n >= nrows) as BF16, loss += scale sum w[n]
+ * (y - Tt)^2 over n < nrows; w = 1 when roww is NULL.  B, Tt, dYt and Yt share
+ * the leading dimension ld.  Yt (Fp x N FP32) is a work array: on long batches y
+ * is not stored.  Errors: MF_ERR_ARG, MF_ERR_HIP. */
+int mf_mlp_loss_grad(int F, int Fp, int64_t N, int64_t nrows, int K, const uint16_t* A, int64_t lda,
+                     const uint16_t* B, const float* bias, const float* Tt, int64_t ld,
+                     const float* roww, float scale, uint16_t* dYt, float* Yt, double* loss,
+                     void* stream);
+
 /* out[m] = (accumulate ? out[m] : 0) + sum_{n<N} X[m*ld + n] for m < M (BF16
  * X, FP32 out): bias gradients.  Errors: MF_ERR_ARG, MF_ERR_HIP. */
 int mf_row_sums(int M, int64_t N, const uint16_t* X, int64_t ld, float* out, int accumulate,

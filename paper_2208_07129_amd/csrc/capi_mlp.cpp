@@ -41,7 +41,17 @@ int mf_mlp_gemm(int M, int N, int K, int ta, int tb, const uint16_t* A, int64_t 
   if (atomic && !out_f32) return fail(MF_ERR_ARG, "atomic needs out_f32");
   if (kchunk > 0 && (bias || relu || mask || out_bf16 || !atomic))
     return fail(MF_ERR_ARG, "a split K range needs atomic FP32 output without epilogue ops");
-  GemmEpi ep{bias, relu, mask, ldmask, out_f32, ld_f32, atomic, out_bf16, ld_bf16, kb};
+  GemmEpi ep{};
+  ep.bias = bias;
+  ep.relu = relu;
+  ep.mask = mask;
+  ep.ldmask = ldmask;
+  ep.out_f32 = out_f32;
+  ep.ld_f32 = ld_f32;
+  ep.atomic = atomic;
+  ep.out_bf16 = out_bf16;
+  ep.ld_bf16 = ld_bf16;
+  ep.kb = kb;
   hipError_t err = launch_gemm_bf16(M, N, K, ta != 0, tb != 0, A, lda, B, ldb, kchunk, ep,
                                     static_cast<hipStream_t>(stream));
   if (err != hipSuccess) return hip_fail(err, "MLP GEMM launch");
@@ -138,6 +148,33 @@ int mf_mse_grad(int F, int Fp, int64_t N, const float* Yt, const float* Tt, int6
   hipError_t err = launch_mse_grad(F, Fp, N, Yt, Tt, ld, roww, scale, dYt, loss,
                                    static_cast<hipStream_t>(stream));
   if (err != hipSuccess) return hip_fail(err, "MSE kernel launch");
+  return MF_OK;
+}
+
+int mf_mlp_loss_grad(int F, int Fp, int64_t N, int64_t nrows, int K, const uint16_t* A, int64_t lda,
+                     const uint16_t* B, const float* bias, const float* Tt, int64_t ld,
+                     const float* roww, float scale, uint16_t* dYt, float* Yt, double* loss,
+                     void* stream) {
+  if (!A || !B || !bias || !Tt || !dYt || !Yt || !loss) return fail(MF_ERR_ARG, "NULL argument");
+  if (F < 1 || Fp < F || Fp % 8 || N < 1 || N % 8 || K < 1 || K % 8)
+    return fail(MF_ERR_ARG, "need 1 <= F <= Fp and Fp, N, K positive multiples of 8");
+  if (nrows < 1 || nrows > N || N > INT32_MAX || ld < N || ld % 8 || lda < K || lda % 8)
+    return fail(MF_ERR_ARG, "need 1 <= nrows <= N <= ld, lda >= K, lda and ld multiples of 8");
+  if (!aligned16(A) || !aligned16(B)) return fail(MF_ERR_ARG, "A, B must be 16-byte aligned");
+  GemmEpi ep{};
+  ep.bias = bias;
+  ep.out_bf16 = dYt;
+  ep.ld_bf16 = ld;
+  ep.target = Tt;
+  ep.ldt = ld;
+  ep.roww = roww;
+  ep.scale = scale;
+  ep.loss = loss;
+  ep.feat = F;
+  ep.nrows = nrows;
+  hipError_t err = launch_gemm_mse(Fp, (int)N, K, A, lda, B, ld, ep, Yt, ld,
+                                   static_cast<hipStream_t>(stream));
+  if (err != hipSuccess) return hip_fail(err, "loss gradient launch");
   return MF_OK;
 }
 

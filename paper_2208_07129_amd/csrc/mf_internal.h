@@ -341,10 +341,23 @@ struct GemmEpi {  // epilogue of the BF16 matrix-core GEMM (see mfmlp.h)
   uint16_t* out_bf16;
   int64_t ld_bf16;
   int kb;  // > 0: B and the outputs in the cell-blocked layout of block width kb
+  // the loss gradient as the output (launch_gemm_mse): targets, row weights (or
+  // NULL), scale, loss, features, rows; out_bf16 takes the gradient
+  const float* target = nullptr;
+  int64_t ldt = 0;
+  const float* roww = nullptr;
+  float scale = 0.f;
+  double* loss = nullptr;
+  int feat = 0;
+  int64_t nrows = 0;
 };
 hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_t* A, int64_t lda,
                             const uint16_t* B, int64_t ldb, int kchunk, const GemmEpi& ep,
                             hipStream_t s);
+// The last layer and the loss gradient: Y = A B + bias only where the fused form is
+// not taken.
+hipError_t launch_gemm_mse(int M, int N, int K, const uint16_t* A, int64_t lda, const uint16_t* B,
+                           int64_t ldb, const GemmEpi& ep, float* Y, int64_t ldy, hipStream_t s);
 hipError_t launch_cell_gather(const Operator& op, int k, const double* R, int64_t ldr,
                               const double* E, int64_t lde, int Fp, uint16_t* X0t, float* Tt,
                               int64_t ldx, float* rho, int pou_sqrt, const double* dsc,

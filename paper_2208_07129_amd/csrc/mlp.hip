@@ -393,7 +393,7 @@ __device__ inline int cell_node_factor(const GridDesc& g, int np, int cx, int cy
 constexpr int kWideMaxM = 4096;   // rows of C, for the bias in LDS
 constexpr int kWideMinN = 32768;  // 128 columns on each of 256 CUs
 constexpr int wide_buffer(int ks, bool ta) { return ta ? 1024 : (ks * 64 + 255) / 256 * 256; }
-enum WideEpi { kWideF32, kWideF32Bias, kWideReluBf16, kWideMaskBf16 };
+enum WideEpi { kWideF32, kWideF32Bias, kWideReluBf16, kWideMaskBf16, kWideMse };
 //
 // CELLS: B is not read but formed, the scaled cell values of an FP64 multivector
 // (column e k + j of B: column j of cell e, row i its local node i, times the
@@ -563,6 +563,7 @@ gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
   // this lane's place in C (rows 4 g .. 4 g + 3 of a step) and the mask, in bytes
   // from a uniform base that moves 16 rows a step
   constexpr bool kF32 = EPI == kWideF32 || EPI == kWideF32Bias;
+  constexpr bool kBias = EPI == kWideF32Bias || EPI == kWideReluBf16 || EPI == kWideMse;
   constexpr int SZ = kF32 ? 4 : 2;
   const int64_t ldc = kF32 ? ep.ld_f32 : ep.ld_bf16;
   const int64_t sc = ep.kb > 0 ? ep.kb : ldc;
@@ -574,8 +575,18 @@ gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
                      : kOob;
   const uint16_t* mbase = EPI == kWideMaskBf16 ? ep.mask + nc : nullptr;
   const int mo = nok ? (int)(uint32_t)(2 * (n - nc + 4 * g * ep.ldmask)) : kOob;
+  // kWideMse: targets in the same way, the row weights (0 past the rows), the loss
+  const float* tbase = EPI == kWideMse ? ep.target + nc : nullptr;
+  const int to = nok ? (int)(uint32_t)(4 * (n - nc + 4 * g * ep.ldt)) : kOob;
+  float rw[NB];
+  double lsum = 0.0;
+  if constexpr (EPI == kWideMse) {
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      rw[j] = n + j < ep.nrows ? (ep.roww ? ep.roww[n + j] : 1.f) : 0.f;
+  }
   stage_load(0);
-  if constexpr (EPI == kWideF32Bias || EPI == kWideReluBf16)
+  if constexpr (kBias)
     for (int i = t; i < (M + 15) / 16 * 16; i += 256) sbias[i] = ep.bias && i < M ? ep.bias[i] : 0.f;
   stage_store(sa);
   stage_load(16);
@@ -600,6 +611,23 @@ gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
         }
       }
     }
+    float tv[4][NB];
+    if constexpr (EPI == kWideMse) {
+      const auto rt = rsrc_of(reinterpret_cast<const uint16_t*>(tbase + (int64_t)m0 * ep.ldt));
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int o = in && m0 + 4 * g + r < ep.feat ? to : kOob;
+        if constexpr (NB == 4) {
+          const auto d = __builtin_amdgcn_raw_buffer_load_b128(rt, o, (int)(4 * r * ep.ldt), 0);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) tv[r][j] = __uint_as_float(d[j]);
+        } else {
+          const auto d = __builtin_amdgcn_raw_buffer_load_b64(rt, o, (int)(4 * r * ep.ldt), 0);
+          tv[r][0] = __uint_as_float(d[0]);
+          tv[r][1] = __uint_as_float(d[1]);
+        }
+      }
+    }
     f32x4 acc[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -613,7 +641,7 @@ gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
                                                          acc[j], 0, 0, 0);
     }
     f32x4 bias;
-    if constexpr (EPI == kWideF32Bias || EPI == kWideReluBf16)
+    if constexpr (kBias)
       bias = *reinterpret_cast<const f32x4*>(&sbias[m0 + 4 * g]);
     const auto rc =
         __builtin_amdgcn_make_buffer_rsrc(cbase + (int64_t)SZ * m0 * sc, 0, kOob, 0x00020000);
@@ -623,10 +651,16 @@ gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         x[j] = acc[j][r];
-        if constexpr (EPI == kWideF32Bias || EPI == kWideReluBf16) x[j] += bias[r];
+        if constexpr (kBias) x[j] += bias[r];
         if constexpr (EPI == kWideReluBf16) x[j] = x[j] > 0.f ? x[j] : 0.f;
         if constexpr (EPI == kWideMaskBf16)
           x[j] = bf16_to_f32((uint16_t)(hm[r][j / 2] >> (16 * (j & 1)))) > 0.f ? x[j] : 0.f;
+        if constexpr (EPI == kWideMse) {
+          const bool live = m0 + 4 * g + r < ep.feat && n + j < ep.nrows;
+          const float d = live ? x[j] - tv[r][j] : 0.f;
+          lsum += (double)rw[j] * d * d;
+          x[j] = 2.0f * ep.scale * rw[j] * d;
+        }
       }
       uint32_t d[kF32 ? NB : NB / 2];
       if constexpr (kF32) {
@@ -647,6 +681,16 @@ gemm_wide_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
         __builtin_amdgcn_raw_buffer_store_b32(d[0], rc, o, so, 0);
     }
     __syncthreads();
+  }
+  if constexpr (EPI == kWideMse) {  // one addition to the loss per workgroup
+    double* part = reinterpret_cast<double*>(wide_sh);
+    part[t] = lsum;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+      if (t < s) part[t] += part[t + s];
+      __syncthreads();
+    }
+    if (t == 0) unsafeAtomicAdd(ep.loss, part[0] * (double)ep.scale);
   }
 }
 
@@ -1188,6 +1232,7 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   const int64_t far_wide = 4 * (16 * (ep.kb > 0 ? ep.kb : ldc) + kbn * (ldc + ldb) + 256 +
                                 (ta ? (int64_t)K : 16) * lda + K + M + 16 * ep.ldmask);
   const int epi = ta ? (ep.mask && !ep.bias && !ep.relu && ep.out_bf16 && vec.mask ? kWideMaskBf16 : -1)
+                  : ep.target ? kWideMse
                   : ep.mask ? -1
                   : ep.relu ? (ep.out_bf16 ? kWideReluBf16 : -1)
                   : ep.out_f32 ? (ep.bias ? kWideF32Bias : kWideF32) : -1;
@@ -1205,6 +1250,7 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
                            dim3(256), lds, s, M, N, K, A, lda, B, ldb, ep, WideCells{});
       };
       if constexpr (TA) run(std::integral_constant<int, kWideMaskBf16>{});
+      else if (epi == kWideMse) run(std::integral_constant<int, kWideMse>{});
       else if (epi == kWideF32) run(std::integral_constant<int, kWideF32>{});
       else if (epi == kWideF32Bias) run(std::integral_constant<int, kWideF32Bias>{});
       else run(std::integral_constant<int, kWideReluBf16>{});
@@ -1238,6 +1284,28 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   else if (big) form(std::integral_constant<int, 128>{}, std::false_type{});
   else form(std::integral_constant<int, 64>{}, std::false_type{});
   return hipGetLastError();
+}
+
+hipError_t launch_gemm_mse(int M, int N, int K, const uint16_t* A, int64_t lda, const uint16_t* B,
+                           int64_t ldb, const GemmEpi& ep, float* Y, int64_t ldy, hipStream_t s) {
+  // Fused where the one-pass kernel takes the product (its conditions in
+  // launch_gemm_bf16) and 16-byte target loads are aligned: the output is neither
+  // written nor read back (a training step of 8000 cells, p = 6, 16 columns: 947 ->
+  // 880 us).
+  const bool fused = N >= kWideMinN && K <= 608 && M <= kWideMaxM && ep.ldt % 4 == 0 &&
+                     ep.ld_bf16 % 4 == 0 && reinterpret_cast<uintptr_t>(ep.target) % 16 == 0 &&
+                     reinterpret_cast<uintptr_t>(ep.out_bf16) % 8 == 0 &&
+                     2 * (128 * lda > 32 * ldb ? 128 * lda : 32 * ldb) + 1024 < (int64_t)1 << 31 &&
+                     4 * (16 * (ep.ld_bf16 + ep.ldt + lda) + 256 + K + M) < (int64_t)1 << 31;
+  if (fused) return launch_gemm_bf16(M, N, K, false, false, A, lda, B, ldb, 0, ep, s);
+  GemmEpi out{};
+  out.bias = ep.bias;
+  out.out_f32 = Y;
+  out.ld_f32 = ldy;
+  hipError_t err = launch_gemm_bf16(M, N, K, false, false, A, lda, B, ldb, 0, out, s);
+  if (err != hipSuccess) return err;
+  return launch_mse_grad(ep.feat, M, ep.nrows, Y, ep.target, ldy, ep.roww, ep.scale, ep.out_bf16,
+                         ep.loss, s);
 }
 
 // Y = S X0 cell by cell, X0 the gathered block (not normalised), in the cell-blocked

@@ -182,13 +182,18 @@ class CellMLP:
                                     int(blocked), _stream_ptr(None)))
         return b
 
-    def forward(self, b):
+    def _hidden(self, b):
         n, Fp, H = b["ld"], self.Fp, self.H
-        W1, b1, W2, b2, W3S, b3 = self.params
+        _, b1, _, b2, _, _ = self.params
         self._gemm(H, n, Fp, False, False, self.wbf[0], Fp, b["X0"], n, bias=b1, relu=True,
                    out_bf16=b["H1"], ld_bf16=n)
         self._gemm(H, n, H, False, False, self.wbf[2], H, b["H1"], n, bias=b2, relu=True,
                    out_bf16=b["H2"], ld_bf16=n)
+
+    def forward(self, b):
+        n, Fp, H = b["ld"], self.Fp, self.H
+        b3 = self.params[5]
+        self._hidden(b)
         self._gemm(Fp, n, H + Fp, False, False, self.wbf[4], H + Fp, b["HX"], n, bias=b3,
                    out_f32=b["Y"], ld_f32=n)
         return b["Y"]
@@ -227,6 +232,17 @@ class CellMLP:
                                  ctypes.c_float(scale), b["dY"].data_ptr(),
                                  self._loss.data_ptr(), _stream_ptr(None)))
 
+    def _last_layer_grad(self, b, roww=None, scale: Optional[float] = None) -> None:
+        """The last layer and loss_grad in one call (b['Y'] is a work array here)."""
+        if scale is None:
+            scale = 1.0 / b["rows"]
+        _check(lib().mf_mlp_loss_grad(self.F, self.Fp, b["ld"], b["rows"], self.H + self.Fp,
+                                      self.wbf[4].data_ptr(), self.H + self.Fp, b["HX"].data_ptr(),
+                                      self.params[5].data_ptr(), b["T"].data_ptr(), b["ld"],
+                                      None if roww is None else roww.data_ptr(),
+                                      ctypes.c_float(scale), b["dY"].data_ptr(),
+                                      b["Y"].data_ptr(), self._loss.data_ptr(), _stream_ptr(None)))
+
     def adam(self, lr: float, b1: float = 0.9, b2: float = 0.999, eps: float = 1e-8):
         self.step += 1
         for i, (w, g, m1, m2) in enumerate(zip(self.params, self.grads, self.m1, self.m2)):
@@ -249,9 +265,9 @@ class CellMLP:
         the Jacobi-correction form E - D^{-1} R; rows weighted by roww); returns
         the loss before the step."""
         b = self.gather(R, T_err)
-        self.forward(b)
+        self._hidden(b)
         self._loss.zero_()
-        self.loss_grad(b, roww, scale)
+        self._last_layer_grad(b, roww, scale)
         self.backward(b)
         self.adam(lr)
         return float(self._loss.item())

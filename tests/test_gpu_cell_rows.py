@@ -80,3 +80,32 @@ def test_mse_grad(F, Fp, N, ld, weights):
     want = 2 * scale * wr * d
     assert bool(((got[:F, :N] - want).abs() <= 2.0 ** -8 * want.abs()).all())
     assert not got[F:, :N].any() and bool((dY[:, N:] == 7).all())
+
+
+@pytest.mark.parametrize("F,N,nrows,K,weights", [(343, 32768, 32761, 600, True),
+                                                 (27, 65536, 65536, 96, True),
+                                                 (125, 33000, 32993, 256, False),
+                                                 (216, 40000, 40000, 352, True),
+                                                 (64, 1032, 1030, 64, True)])
+def test_last_layer_with_its_loss_gradient(F, N, nrows, K, weights):
+    """The bits of the product followed by the loss gradient (long batches form it in the
+    product's epilogue); the loss up to the order of its double sums."""
+    Fp = (F + 7) // 8 * 8
+    A = torch.randn(Fp, K, device="cuda").to(torch.bfloat16).view(torch.int16)
+    B = torch.randn(K, N, device="cuda").to(torch.bfloat16).view(torch.int16)
+    bias, T = torch.randn(Fp, device="cuda"), torch.randn(Fp, N, device="cuda")
+    w = torch.rand(N, device="cuda") if weights else None
+    wp, s, lib = None if w is None else w.data_ptr(), 0.125, mfmv.lib()
+    loss = torch.zeros(2, dtype=torch.float64, device="cuda")
+    Y, Yw = torch.zeros(2, Fp, N, device="cuda")
+    d0, d1 = torch.zeros(2, Fp, N, dtype=torch.int16, device="cuda")
+    mlp.CellMLP._gemm(Fp, N, K, False, False, A, K, B, N, bias=bias, out_f32=Y, ld_f32=N)
+    mfmv._check(lib.mf_mse_grad(F, Fp, nrows, Y.data_ptr(), T.data_ptr(), N, wp, s, d0.data_ptr(),
+                                loss[:1].data_ptr(), None))
+    mfmv._check(lib.mf_mlp_loss_grad(F, Fp, N, nrows, K, A.data_ptr(), K, B.data_ptr(),
+                                     bias.data_ptr(), T.data_ptr(), N, wp, s, d1.data_ptr(),
+                                     Yw.data_ptr(), loss[1:].data_ptr(), None))
+    torch.cuda.synchronize()
+    assert torch.equal(d0, d1)
+    a, b = loss.tolist()
+    assert abs(a - b) <= 1e-12 * a
