@@ -60,10 +60,10 @@ hipError_t launch_box(const ApplyLaunch& a, hipStream_t s) {
   // Assembly along the rows (box_p8_rows): its extra LDS stage lengthens a lone
   // item, so tiles of four columns and cells of nine points take it only on meshes
   // that fill the chip.  Without and with it, one column: p = 6, 16^3 72 / 47 us, 6^3
-  // 20 / 18; p = 8, 12^3 62 / 43, 4^3 19 / 20; two: p = 8, 12^3 62 / 54, 4^3 19 / 22;
+  // 20 / 18, 4^3 15.3 / 16.1; p = 8, 12^3 62 / 43, 4^3 19 / 20; two: p = 8, 12^3 62 / 54, 4^3 19 / 22;
   // four: p = 6, 16^3 75 / 69, 6^3 19 / 20; p = 4, 24^3 93 / 85; p = 8, 12^3 70 / 78.
   constexpr bool rows_built = !PERS && C == 1 && B <= (NP >= 9 ? 2 : 4);
-  constexpr int64_t rows_min = B <= 2 && NP <= 8 ? 0 : 1024;
+  constexpr int64_t rows_min = B <= 2 && NP <= 8 ? 128 : 1024;
   Kern k;
   if constexpr (PERS) k = apply_box_pers_kernel<NP, NQ, B, C, NT, ACCUM>;
   else k = apply_box_kernel<NP, NQ, B, C, NT, ACCUM, false>;

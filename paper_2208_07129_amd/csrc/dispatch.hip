@@ -1,4 +1,6 @@
 // Dispatch of the fused apply by polynomial degree, and the zero-fill kernel.
+#include <algorithm>
+
 #include "mf_internal.h"
 #include "sf_common.h"
 
@@ -47,8 +49,9 @@ __global__ void __launch_bounds__(256) fma_probe_kernel(int64_t iters, double se
   out[(int64_t)blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
-// Node lines (gy, gz) of the Nx x Ny x Nz grid, each taken whole by one
-// workgroup (a grid-stride loop when the grid is smaller than the line count).
+// Node lines (gy, gz) of the Nx x Ny x Nz grid, each taken whole by `team`
+// threads, a workgroup or one of its wavefronts (a grid-stride loop when there are
+// fewer teams than lines).
 // A line on a shared plane (gz a multiple of p, gy a multiple of py or equal to
 // ylast) is zeroed whole; otherwise only the rows gx = 0, p, 2p, ... are.  Threads form (row, column)
 // pairs, the columns of a row on cw = 2^cw_log2 consecutive lanes (the next
@@ -57,12 +60,14 @@ __global__ void __launch_bounds__(256) fma_probe_kernel(int64_t iters, double se
 // cell-interior nodes are skipped: the box kernel writes them.
 __global__ void zero_shared_rows_kernel(double* __restrict__ Y, int Nx, int Ny, int p, int py,
                                         int ylast, int ncols, int64_t ld, int64_t lines,
-                                        int cw_log2) {
+                                        int cw_log2, int team) {
   const int cw = 1 << cw_log2;
-  const int c0 = threadIdx.x & (cw - 1);
-  const int r0 = threadIdx.x >> cw_log2, rstep = blockDim.x >> cw_log2;
-  for (int64_t line = blockIdx.x; line < lines; line += gridDim.x) {
-    const int gy = (int)(line % Ny), gz = (int)(line / Ny);
+  const int t = threadIdx.x & (team - 1), teams = blockDim.x / team;
+  const int c0 = t & (cw - 1);
+  const int r0 = t >> cw_log2, rstep = team >> cw_log2;
+  for (int64_t line = (int64_t)blockIdx.x * teams + threadIdx.x / team; line < lines;
+       line += (int64_t)gridDim.x * teams) {
+    const int gz = (int)((uint32_t)line / (uint32_t)Ny), gy = (int)line - gz * Ny;
     const bool full = (gy % py == 0) || gy == ylast || (gz % p == 0);
     const int step = full ? 1 : p;
     const int nrows = full ? Nx : (Nx + p - 1) / p;
@@ -226,6 +231,7 @@ static int last_face_y(const int64_t* nodes, int p) {
   return nodes[1] % p == 1 || p == 1 ? (int)nodes[1] - 1 : -1;
 }
 
+constexpr int64_t kNarrowLine = 512;  // rows times columns of a line
 hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int py, int ncols,
                                    int64_t ld, hipStream_t s) {
   const int64_t lines = nodes[1] * nodes[2];
@@ -237,9 +243,14 @@ hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int
   int64_t wgs = nodes[0] * lines * ncols / 2048;
   if (wgs < 256) wgs = 256;
   if (wgs > lines) wgs = lines;
+  // Lines of few elements go to single wavefronts, a line or a few each: with a
+  // workgroup per line most of its threads have no row (one column, between events: p = 6,
+  // 16^3 12.9 -> 7.2 us, 30^3 23 -> 13; four columns, 16^3 10.8 -> 8.0).
+  const bool narrow = nodes[0] << cw_log2 <= kNarrowLine;
+  if (narrow) wgs = std::min<int64_t>((lines + 3) / 4, 4096);
   hipLaunchKernelGGL(zero_shared_rows_kernel, dim3((unsigned)wgs), dim3(256), 0, s, Y,
-                     (int)nodes[0], (int)nodes[1], p, py,
-                     last_face_y(nodes, p), ncols, ld, lines, cw_log2);
+                     (int)nodes[0], (int)nodes[1], p, py, last_face_y(nodes, p), ncols, ld, lines,
+                     cw_log2, narrow ? 64 : 256);
   return hipGetLastError();
 }
 
