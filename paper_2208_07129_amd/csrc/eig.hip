@@ -142,7 +142,13 @@ bj_norm_kernel(int K, const double* __restrict__ Aw, double* __restrict__ part, 
 // rotate the off-diagonal blocks, (i, j) and (j, i) per lane; four hold the
 // rotation V in registers (lane = row, a wavefront = eight slot pairs) and pass
 // two columns each to their neighbours.  155 us a launch with separate row and
-// column passes and three barriers, 64 so.
+// column passes and three barriers, 64.6 so with the 13 next to each other.
+//
+// What a round then waits for is instruction issue: wavefronts go to the four SIMDs in
+// turn, which put the angles (by instruction count 800 of a round's 2400 cycles), two of
+// the blocks (370 each) and one of V (420) on the first.  With three empty wavefronts in
+// between, the first SIMD has the angles and one of V only, the others two or three of
+// blocks and one of V: 53.9 us a launch.
 //
 // The arithmetic is that of the plain cyclic sweep, element by element: rows, then
 // columns, p the smaller index of a pair, ap' = fma(c, ap, -(s aq)) and aq' =
@@ -153,8 +159,9 @@ bj_norm_kernel(int K, const double* __restrict__ Aw, double* __restrict__ part, 
 constexpr int kBjP2 = kBjPair / 2;  // slot pairs
 constexpr int kBjRow = kBjP2 + 1, kBjPlane = kBjP2 * kBjRow;
 constexpr int kBjAWaves = 8, kBjVWaves = 4;  // wavefronts on the blocks, on V
-constexpr int kBjSweepThreads = 64 * (1 + kBjAWaves + kBjVWaves);
+constexpr int kBjSweepThreads = 1024;       // with the empty ones
 constexpr size_t kBjSweepLds = 2 * 4 * (size_t)kBjPlane * sizeof(double);
+static_assert(kBjAWaves + kBjVWaves <= 12, "three of every four wavefronts, and the fifth");
 static_assert(kBjP2 * (kBjP2 - 1) / 2 <= 64 * kBjAWaves, "two off-diagonal blocks per lane");
 static_assert(2 * 4 * kBjPlane >= kBjPair * kBjLd, "V is written out through the blocks' LDS");
 
@@ -211,6 +218,15 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
   const int t = threadIdx.x, nb = K / kBj, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   constexpr int kRounds = kBjPair - 1;
+  // the angles, blocks 1 .., V, or (above) nothing to do
+  int role = 1 + kBjAWaves + kBjVWaves;
+  if ((wave & 3) == 0) {
+    if (wave == 0) role = 0;
+    if (wave == 4) role = kBjAWaves + kBjVWaves;
+  } else {
+    const int n = (wave >> 2) * 3 + (wave & 3);  // 1..12
+    if (n < kBjAWaves + kBjVWaves) role = n;
+  }
   int P, Q;
   round_robin(nb, r, blockIdx.x, P, Q);
   for (int i = t; i < kBjPair * kBjPair; i += kBjSweepThreads) {
@@ -221,7 +237,7 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
         Aw[(int64_t)pair_index(P, Q, row) * K + pair_index(P, Q, col)];
   }
   __syncthreads();
-  if (wave == 0) {
+  if (role == 0) {
     __builtin_amdgcn_s_setprio(3);  // the chain that every round waits for
     const int p = lane & (kBjP2 - 1), dia = p * kBjRow + p;
     // the pair's block, [slot][slot]
@@ -289,10 +305,10 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
     }
     __syncthreads();
     __syncthreads();
-  } else if (wave <= kBjAWaves) {
+  } else if (role <= kBjAWaves) {
     // off-diagonal blocks (pi, pj) and (pj, pi), pi < pj: rows fr and 30 - fr of the
     // triangle fill 32 lanes
-    const int e = t - 64, fr = e / kBjP2, fk = e % kBjP2;
+    const int e = (role - 1) * 64 + lane, fr = e / kBjP2, fk = e % kBjP2;
     const bool upper = fk < kBjP2 - 1 - fr;
     const int pi = upper ? fr : kBjP2 - 2 - fr, pj = upper ? fr + 1 + fk : fk;
     const bool on = fr < kBjP2 / 2 - 1 || upper;
@@ -333,9 +349,11 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
     }
     __syncthreads();
     __syncthreads();
+  } else if (role > kBjAWaves + kBjVWaves) {  // as many barriers as the others
+    for (int rr = 0; rr < kRounds + 2; ++rr) __syncthreads();
   } else {
     constexpr int G = kBjP2 / kBjVWaves;  // slot pairs of a wavefront
-    const int g = wave - 1 - kBjAWaves;
+    const int g = role - 1 - kBjAWaves;
     double top[G], bot[G];
 #pragma unroll
     for (int k = 0; k < G; ++k) {
