@@ -58,7 +58,7 @@ constexpr int kKStep = 32, kPad = 40;  // LDS rows of 80 bytes
 // reads meet on a bank.  Without TB the matrix instruction takes B as its first
 // operand, so a lane holds four consecutive columns of C and stores 16 bytes.
 //
-// 344 x 600 x 128000 (TB, split K): 146 us, 361 TFLOP/s (64 x 64 tiles with
+// 344 x 600 x 128000 (TB, 16 pieces of K): 131 us, 403 TFLOP/s (64 x 64 tiles with
 // element-wise transposing stores and loads selected after they arrive: 250).
 struct GemmVec {  // whether the tiled kernel's outputs take 4-element stores and its mask 4-element loads
   int f32, bf16, mask;
@@ -1195,27 +1195,23 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   const bool split = kchunk > 0;
   if (kchunk <= 0 || kchunk > K) kchunk = K;
   kchunk = (kchunk + kKStep - 1) / kKStep * kKStep;
-  int kz = (K + kchunk - 1) / kchunk;
+  const int kz = (K + kchunk - 1) / kchunk;
   auto tiles_of = [&](int t) { return ((int64_t)N + t - 1) / t * (((int64_t)M + t - 1) / t); };
   // Tiles of 128 once they give every CU two workgroups, tiles of 64 below that
-  // (344 x 8000 x 344: 20 us with 64, 22 with 128; 31000 columns: 38 and 33; 344 x
-  // 600 x 128000 in pieces: 181 and 148).  A split K range may be cut further to get there, in pieces of
-  // at least 1024: each piece adds its tile once more.
-  constexpr int kFill = 512, kMinPiece = 1024;
-  if (split && tiles_of(128) * kz < kFill && K > kMinPiece) {
-    const int64_t want = (kFill + tiles_of(128) - 1) / tiles_of(128);
-    int64_t piece = (K + want - 1) / want;
-    if (piece < kMinPiece) piece = kMinPiece;
-    if (piece < kchunk) kchunk = (int)((piece + kKStep - 1) / kKStep * kKStep);
-    kz = (K + kchunk - 1) / kchunk;
-  }
+  // (344 x 8000 x 344: 20 us with 64, 22 with 128; 31000 columns: 38 and 33).  Long pieces of a
+  // split K range: once the pieces fill most of the CUs, as one round of 128-row tiles
+  // (131 us with pieces of 8192) then takes less than the several of the others (344 x 600
+  // x 128000, 240 tiles of 128: 146 us with 64, 131 with 128; 256 x 344 x 262144, 192: 148 and
+  // 154; 256 x 256 x 128000, 64: 70 and 130).  The pieces are the caller's: each adds its
+  // FP32 sum once, so another cut would round the results differently.
+  constexpr int kFill = 512, kFillSplit = 224, kLongPiece = 4096;
   // the 32-bit offsets of a step: T rows of an operand with k along the rows, 32
   // k rows otherwise (in blocks: 32 rows of a block and the tile's later blocks)
   const int64_t span_a = (ta ? 32 : 128) * lda;
   const int64_t span_b = tb ? 128 * ldb
                             : ep.kb > 0 ? (int64_t)32 * ep.kb + (128 / ep.kb + 1) * ldb : 32 * ldb;
   const bool far = 2 * (span_a > span_b ? span_a : span_b) + 1024 >= (int64_t)1 << 31;
-  const bool big = !far && tiles_of(128) * kz >= kFill;
+  const bool big = !far && tiles_of(128) * kz >= (split && kchunk >= kLongPiece ? kFillSplit : kFill);
   const int64_t total = tiles_of(big ? 128 : 64) * kz;
   const dim3 grid((unsigned)((total + kXcds - 1) / kXcds * kXcds));
   auto al = [](const void* p, int64_t ld, int kb, size_t n) {
