@@ -1054,42 +1054,47 @@ mse_grad_kernel(int F, int Fp, int64_t nrows, const float* __restrict__ Yt,
   if (threadIdx.x == 0) unsafeAtomicAdd(loss, part[0] * (double)scale);
 }
 
-// out[m] (+)= sum_n X[m][n] (BF16 rows): bias gradients.  One workgroup per row,
-// 16 bytes a load where VEC says that rows start on that boundary, four loads in
-// flight: 256 x 128000: 12 us (with 256 threads and single elements 131).
-constexpr int kRowThreads = 1024;
+// out[m] (+)= sum_n X[m][n] (BF16 rows): bias gradients.  The order of the sum is
+// fixed: 256 partial sums, number r over the n = r mod 256 in order, then a tree (the
+// optimiser divides a gradient by its own size, so another order of the FP32 sums
+// would show in the weights).  One workgroup per row, a thread for two neighbouring
+// partial sums where VEC says that rows start on 4 bytes, kAhead loads in flight, which
+// is what it takes to cover the latency of a few wavefronts per CU.  256 x 128000:
+// 19 us (256 threads, one element in flight each, 120).
+constexpr int kRowParts = 256;
 template <bool VEC>
-__global__ void __launch_bounds__(kRowThreads)
+__global__ void __launch_bounds__(kRowParts / (VEC ? 2 : 1))
 row_sums_kernel(int64_t N, const uint16_t* __restrict__ X, int64_t ld, float* __restrict__ out,
                 int accumulate) {
-  __shared__ float part[kRowThreads];
+  constexpr int W = VEC ? 2 : 1, kAhead = 32;
+  __shared__ float part[kRowParts];
   const int m = blockIdx.x;
   const uint16_t* row = X + (int64_t)m * ld;
-  const int64_t whole = VEC ? N / 8 : 0;  // chunks of 8
-  constexpr int U = 4;
-  float acc[U];
+  float acc[W];
 #pragma unroll
-  for (int u = 0; u < U; ++u) acc[u] = 0.f;
-  auto add = [&](float& a, uint4 x) {
-    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+  for (int w = 0; w < W; ++w) acc[w] = 0.f;
+  int64_t n = W * (int64_t)threadIdx.x;
+  for (; n + (kAhead - 1) * kRowParts + W <= N; n += kAhead * kRowParts) {
+    uint32_t x[kAhead];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      a += __uint_as_float(w[i] << 16) + __uint_as_float(w[i] & 0xffff0000u);
-  };
-  int64_t n = threadIdx.x;
-  for (; n + (U - 1) * kRowThreads < whole; n += U * kRowThreads) {
-    uint4 x[U];
+    for (int u = 0; u < kAhead; ++u) {
+      if constexpr (VEC) x[u] = *reinterpret_cast<const uint32_t*>(row + n + u * kRowParts);
+      else x[u] = row[n + u * kRowParts];
+    }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      x[u] = *reinterpret_cast<const uint4*>(row + 8 * (n + u * kRowThreads));
-#pragma unroll
-    for (int u = 0; u < U; ++u) add(acc[u], x[u]);
+    for (int u = 0; u < kAhead; ++u) {
+      acc[0] += __uint_as_float(x[u] << 16);
+      if constexpr (VEC) acc[1] += __uint_as_float(x[u] & 0xffff0000u);
+    }
   }
-  for (; n < whole; n += kRowThreads) add(acc[0], *reinterpret_cast<const uint4*>(row + 8 * n));
-  for (n = 8 * whole + threadIdx.x; n < N; n += kRowThreads) acc[1] += bf16_to_f32(row[n]);
-  part[threadIdx.x] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  for (; n < N; n += kRowParts)
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+      if (n + w < N) acc[w] += bf16_to_f32(row[n + w]);
+#pragma unroll
+  for (int w = 0; w < W; ++w) part[W * threadIdx.x + w] = acc[w];
   __syncthreads();
-  for (int s = kRowThreads / 2; s > 0; s >>= 1) {
+  for (int s = kRowParts / 2; s > 0; s >>= 1) {
     if (threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
     __syncthreads();
   }
@@ -1444,12 +1449,12 @@ hipError_t launch_mse_grad(int F, int Fp, int64_t nrows, const float* Yt, const 
 
 hipError_t launch_row_sums(int M, int64_t N, const uint16_t* X, int64_t ld, float* out,
                            bool accumulate, hipStream_t s) {
-  const bool vec = ld % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+  const bool vec = ld % 2 == 0 && reinterpret_cast<uintptr_t>(X) % 4 == 0;
   if (vec)
-    hipLaunchKernelGGL((row_sums_kernel<true>), dim3(M), dim3(kRowThreads), 0, s, N, X, ld, out,
+    hipLaunchKernelGGL((row_sums_kernel<true>), dim3(M), dim3(kRowParts / 2), 0, s, N, X, ld, out,
                        accumulate ? 1 : 0);
   else
-    hipLaunchKernelGGL((row_sums_kernel<false>), dim3(M), dim3(kRowThreads), 0, s, N, X, ld, out,
+    hipLaunchKernelGGL((row_sums_kernel<false>), dim3(M), dim3(kRowParts), 0, s, N, X, ld, out,
                        accumulate ? 1 : 0);
   return hipGetLastError();
 }
