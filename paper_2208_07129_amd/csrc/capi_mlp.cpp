@@ -145,7 +145,7 @@ int mf_mse_grad(int F, int Fp, int64_t N, const float* Yt, const float* Tt, int6
                 const float* roww, float scale, uint16_t* dYt, double* loss, void* stream) {
   if (!Yt || !Tt || !dYt || !loss) return fail(MF_ERR_ARG, "NULL argument");
   if (F < 1 || Fp < F || N < 1 || ld < N) return fail(MF_ERR_ARG, "need 1 <= F <= Fp, 1 <= N <= ld");
-  hipError_t err = launch_mse_grad(F, Fp, N, Yt, Tt, ld, roww, scale, dYt, loss,
+  hipError_t err = launch_mse_grad(F, Fp, N, N, Yt, Tt, ld, roww, scale, dYt, loss,
                                    static_cast<hipStream_t>(stream));
   if (err != hipSuccess) return hip_fail(err, "MSE kernel launch");
   return MF_OK;

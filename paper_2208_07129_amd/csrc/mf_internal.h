@@ -370,9 +370,9 @@ hipError_t launch_cell_scatter(const Operator& op, int k, const float* Yt, int64
                                double* Z, int64_t ldz, int pou_sqrt, const double* dsc,
                                int blocked, hipStream_t s);
 hipError_t launch_symmetrize(int n, float* S, int64_t ld, uint16_t* Sbf, hipStream_t s);
-hipError_t launch_mse_grad(int F, int Fp, int64_t nrows, const float* Yt, const float* Tt,
-                           int64_t ld, const float* roww, float scale, uint16_t* dYt, double* loss,
-                           hipStream_t s);
+hipError_t launch_mse_grad(int F, int Fp, int64_t nrows, int64_t ncols, const float* Yt,
+                           const float* Tt, int64_t ld, const float* roww, float scale,
+                           uint16_t* dYt, double* loss, hipStream_t s);
 hipError_t launch_row_sums(int M, int64_t N, const uint16_t* X, int64_t ld, float* out,
                            bool accumulate, hipStream_t s);
 hipError_t launch_adam(int64_t n, float* w, const float* g, float* m1, float* m2, uint16_t* wbf,

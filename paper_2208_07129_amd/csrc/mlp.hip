@@ -998,19 +998,19 @@ node_assemble_kernel(AsmArgs a, int nlines, int nchunks) {
   else assemble_line<P, 2, 2, BLK, RHO, DIAG>(a, cx, gy, gz, cy, ly, wy, cz, lz, wz, j, jok);
 }
 
-// dYt = 2 scale w[n] (Yt - Tt) for features < F (0 for the padding), as
-// BF16; loss += scale sum w[n] (Yt - Tt)^2 (w = 1 when the row weights are
+// dYt = 2 scale w[n] (Yt - Tt) for features < F (0 for the padding features and in
+// the columns from nrows to ncols), as BF16; loss += scale sum w[n] (Yt - Tt)^2 (w = 1 when the row weights are
 // null).  Pieces of one feature by 4 x 256 batch rows, 16-byte loads and 8-byte
 // stores where VEC says that every row starts on such a boundary.  Bound by
 // memory (344 x 128000: 92 us, 4.8 TB/s).
 template <bool VEC>
 __global__ void __launch_bounds__(256)
-mse_grad_kernel(int F, int Fp, int64_t nrows, const float* __restrict__ Yt,
+mse_grad_kernel(int F, int Fp, int64_t nrows, int64_t ncols, const float* __restrict__ Yt,
                 const float* __restrict__ Tt, int64_t ld, const float* __restrict__ roww,
                 float scale, uint16_t* __restrict__ dYt, double* __restrict__ loss) {
   __shared__ double part[256];
   double acc = 0.0;
-  const int64_t chunks = (nrows + 1023) / 1024, pieces = chunks * Fp;
+  const int64_t chunks = (ncols + 1023) / 1024, pieces = chunks * Fp;
   for (int64_t u = blockIdx.x; u < pieces; u += gridDim.x) {
     const int i = (int)(u / chunks);
     const int64_t n = (u - i * chunks) * 1024 + 4 * threadIdx.x;
@@ -1034,10 +1034,11 @@ mse_grad_kernel(int F, int Fp, int64_t nrows, const float* __restrict__ Yt,
       h.w = f32_to_bf16(2.0f * scale * w[3] * d[3]);
       *reinterpret_cast<ushort4*>(dYt + o) = h;
     } else {
-      for (int r = 0; r < 4 && n + r < nrows; ++r) {
-        const float w = roww ? roww[n + r] : 1.0f;
+      for (int r = 0; r < 4 && n + r < ncols; ++r) {
+        const bool live = n + r < nrows;
+        const float w = roww && live ? roww[n + r] : 1.0f;
         float d = 0.f;
-        if (i < F) {
+        if (i < F && live) {
           d = Yt[o + r] - Tt[o + r];
           acc += (double)w * d * d;
         }
@@ -1305,7 +1306,7 @@ hipError_t launch_gemm_mse(int M, int N, int K, const uint16_t* A, int64_t lda, 
   out.ld_f32 = ldy;
   hipError_t err = launch_gemm_bf16(M, N, K, false, false, A, lda, B, ldb, 0, out, s);
   if (err != hipSuccess) return err;
-  return launch_mse_grad(ep.feat, M, ep.nrows, Y, ep.target, ldy, ep.roww, ep.scale, ep.out_bf16,
+  return launch_mse_grad(ep.feat, M, ep.nrows, N, Y, ep.target, ldy, ep.roww, ep.scale, ep.out_bf16,
                          ep.loss, s);
 }
 
@@ -1432,17 +1433,17 @@ hipError_t launch_cell_scatter(const Operator& op, int k, const float* Yt, int64
   return hipGetLastError();
 }
 
-hipError_t launch_mse_grad(int F, int Fp, int64_t nrows, const float* Yt, const float* Tt,
-                           int64_t ld, const float* roww, float scale, uint16_t* dYt, double* loss,
-                           hipStream_t s) {
+hipError_t launch_mse_grad(int F, int Fp, int64_t nrows, int64_t ncols, const float* Yt,
+                           const float* Tt, int64_t ld, const float* roww, float scale,
+                           uint16_t* dYt, double* loss, hipStream_t s) {
   auto at = [](const void* p, size_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
-  const int64_t pieces = (nrows + 1023) / 1024 * Fp;
+  const int64_t pieces = (ncols + 1023) / 1024 * Fp;
   const dim3 grid((unsigned)std::min<int64_t>(pieces, 2048));  // one addition to loss each
   if (ld % 4 == 0 && at(Yt, 16) && at(Tt, 16) && at(roww, 16) && at(dYt, 8))
-    hipLaunchKernelGGL((mse_grad_kernel<true>), grid, dim3(256), 0, s, F, Fp, nrows, Yt, Tt, ld,
+    hipLaunchKernelGGL((mse_grad_kernel<true>), grid, dim3(256), 0, s, F, Fp, nrows, ncols, Yt, Tt, ld,
                        roww, scale, dYt, loss);
   else
-    hipLaunchKernelGGL((mse_grad_kernel<false>), grid, dim3(256), 0, s, F, Fp, nrows, Yt, Tt, ld,
+    hipLaunchKernelGGL((mse_grad_kernel<false>), grid, dim3(256), 0, s, F, Fp, nrows, ncols, Yt, Tt, ld,
                        roww, scale, dYt, loss);
   return hipGetLastError();
 }
