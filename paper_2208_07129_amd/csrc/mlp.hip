@@ -1193,6 +1193,46 @@ unsigned blocks_for(int64_t total) {
   return (unsigned)(b < 1 ? 1 : b);
 }
 
+// Whether stores of four elements (and loads of the mask) are aligned.
+bool aligned4(const void* p, int64_t ld, int kb, size_t n) {
+  return reinterpret_cast<uintptr_t>(p) % n == 0 && ld % 4 == 0 && kb % 4 == 0;
+}
+GemmVec gemm_vec(const GemmEpi& ep) {
+  return {aligned4(ep.out_f32, ep.ld_f32, ep.kb, 16), aligned4(ep.out_bf16, ep.ld_bf16, ep.kb, 8),
+          aligned4(ep.mask, ep.ldmask, 0, 8)};
+}
+// The operands' offsets of one tiled step in 32 bits: T rows of an operand with k
+// along the rows, 32 k rows otherwise (in blocks: 32 rows of a block and the tile's
+// later blocks).
+bool gemm_far(bool ta, bool tb, int64_t lda, int64_t ldb, int kb) {
+  const int64_t span_a = (ta ? 32 : 128) * lda;
+  const int64_t span_b =
+      tb ? 128 * ldb : kb > 0 ? (int64_t)32 * kb + (128 / kb + 1) * ldb : 32 * ldb;
+  return 2 * (span_a > span_b ? span_a : span_b) + 1024 >= (int64_t)1 << 31;
+}
+
+// The epilogue with which the one-pass kernel can take a product (-1: it cannot): the one
+// place where its limits stand, for the dispatch and for the callers that need it (the
+// tiled kernel knows no targets).
+int wide_epi(int M, int N, int K, bool ta, bool tb, int64_t lda, int64_t ldb, const GemmEpi& ep) {
+  const GemmVec vec = gemm_vec(ep);
+  if (tb || ep.atomic || N < kWideMinN || M > kWideMaxM || K > (ta ? 352 : 608)) return -1;
+  if (ep.out_f32 ? ep.out_bf16 || !vec.f32 : !vec.bf16) return -1;
+  const int64_t kbn = ep.kb > 0 ? 256 / ep.kb + 1 : 0;  // blocks that a wavefront may touch
+  const int64_t ldc = ep.out_f32 ? ep.ld_f32 : ep.ld_bf16;
+  const int64_t far_wide = 4 * (16 * (ep.kb > 0 ? ep.kb : ldc) + kbn * (ldc + ldb) + 256 +
+                                (ta ? (int64_t)K : 16) * lda + K + M + 16 * ep.ldmask +
+                                (ep.target ? 16 * ep.ldt : 0));
+  if (gemm_far(ta, tb, lda, ldb, ep.kb) || far_wide >= (int64_t)1 << 31) return -1;
+  if (ep.target)
+    return !ta && !ep.kb && !ep.mask && !ep.relu && ep.out_bf16 && aligned4(ep.target, ep.ldt, 0, 16)
+               ? kWideMse : -1;
+  if (ta) return ep.mask && !ep.bias && !ep.relu && ep.out_bf16 && vec.mask ? kWideMaskBf16 : -1;
+  if (ep.mask) return -1;
+  if (ep.relu) return ep.out_bf16 ? kWideReluBf16 : -1;
+  return ep.out_f32 ? (ep.bias ? kWideF32Bias : kWideF32) : -1;
+}
+
 }  // namespace
 
 hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_t* A, int64_t lda,
@@ -1211,36 +1251,17 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   // 154; 256 x 256 x 128000, 64: 70 and 130).  The pieces are the caller's: each adds its
   // FP32 sum once, so another cut would round the results differently.
   constexpr int kFill = 512, kFillSplit = 224, kLongPiece = 4096;
-  // the 32-bit offsets of a step: T rows of an operand with k along the rows, 32
-  // k rows otherwise (in blocks: 32 rows of a block and the tile's later blocks)
-  const int64_t span_a = (ta ? 32 : 128) * lda;
-  const int64_t span_b = tb ? 128 * ldb
-                            : ep.kb > 0 ? (int64_t)32 * ep.kb + (128 / ep.kb + 1) * ldb : 32 * ldb;
-  const bool far = 2 * (span_a > span_b ? span_a : span_b) + 1024 >= (int64_t)1 << 31;
+  const bool far = gemm_far(ta, tb, lda, ldb, ep.kb);
   const bool big = !far && tiles_of(128) * kz >= (split && kchunk >= kLongPiece ? kFillSplit : kFill);
   const int64_t total = tiles_of(big ? 128 : 64) * kz;
   const dim3 grid((unsigned)((total + kXcds - 1) / kXcds * kXcds));
-  auto al = [](const void* p, int64_t ld, int kb, size_t n) {
-    return reinterpret_cast<uintptr_t>(p) % n == 0 && (ld % 4 == 0) && kb % 4 == 0;
-  };
-  const GemmVec vec{al(ep.out_f32, ep.ld_f32, ep.kb, 16), al(ep.out_bf16, ep.ld_bf16, ep.kb, 8),
-                    al(ep.mask, ep.ldmask, 0, 8)};
   // A long batch takes the one-pass kernel, with 128 columns per workgroup as soon
   // as that gives every CU one (256 x 32768 x 344: 26 us, tiled 30; 16384 columns:
   // 22.6 and 21.8), with 256 from twice as many on (128000 columns: 45 us, 48 with
   // 128; 65536: 35 and 34).
-  const int64_t kbn = ep.kb > 0 ? 256 / ep.kb + 1 : 0;  // blocks that a wavefront may touch
-  const int64_t ldc = ep.out_f32 ? ep.ld_f32 : ep.ld_bf16;
-  const int64_t far_wide = 4 * (16 * (ep.kb > 0 ? ep.kb : ldc) + kbn * (ldc + ldb) + 256 +
-                                (ta ? (int64_t)K : 16) * lda + K + M + 16 * ep.ldmask);
-  const int epi = ta ? (ep.mask && !ep.bias && !ep.relu && ep.out_bf16 && vec.mask ? kWideMaskBf16 : -1)
-                  : ep.target ? kWideMse
-                  : ep.mask ? -1
-                  : ep.relu ? (ep.out_bf16 ? kWideReluBf16 : -1)
-                  : ep.out_f32 ? (ep.bias ? kWideF32Bias : kWideF32) : -1;
-  const bool one_out = ep.out_f32 ? !ep.out_bf16 && vec.f32 : vec.bf16;
-  if (!tb && !ep.atomic && !far && far_wide < (int64_t)1 << 31 && epi >= 0 && one_out &&
-      M <= kWideMaxM && K <= (ta ? 352 : 608) && N >= kWideMinN) {
+  const int epi = wide_epi(M, N, K, ta, tb, lda, ldb, ep);
+  if (ep.target && epi < 0) return hipErrorInvalidValue;
+  if (epi >= 0) {
     auto wide = [&](auto ksc, auto nbc, auto tac) {
       constexpr int KS = decltype(ksc)::value, NB = decltype(nbc)::value;
       constexpr bool TA = decltype(tac)::value;
@@ -1274,7 +1295,7 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   auto go = [&](auto tc, auto fa, auto fb, auto fr) {
     hipLaunchKernelGGL((gemm_bf16_kernel<decltype(tc)::value, decltype(fa)::value,
                                          decltype(fb)::value, decltype(fr)::value>),
-                       grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, kchunk, ep, vec);
+                       grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, kchunk, ep, gemm_vec(ep));
   };
   auto form = [&](auto tc, auto fr) {
     if (!ta && !tb) go(tc, std::false_type{}, std::false_type{}, fr);
@@ -1290,16 +1311,11 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
 
 hipError_t launch_gemm_mse(int M, int N, int K, const uint16_t* A, int64_t lda, const uint16_t* B,
                            int64_t ldb, const GemmEpi& ep, float* Y, int64_t ldy, hipStream_t s) {
-  // Fused where the one-pass kernel takes the product (its conditions in
-  // launch_gemm_bf16) and 16-byte target loads are aligned: the output is neither
-  // written nor read back (a training step of 8000 cells, p = 6, 16 columns: 947 ->
-  // 880 us).
-  const bool fused = N >= kWideMinN && K <= 608 && M <= kWideMaxM && ep.ldt % 4 == 0 &&
-                     ep.ld_bf16 % 4 == 0 && reinterpret_cast<uintptr_t>(ep.target) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(ep.out_bf16) % 8 == 0 &&
-                     2 * (128 * lda > 32 * ldb ? 128 * lda : 32 * ldb) + 1024 < (int64_t)1 << 31 &&
-                     4 * (16 * (ep.ld_bf16 + ep.ldt + lda) + 256 + K + M) < (int64_t)1 << 31;
-  if (fused) return launch_gemm_bf16(M, N, K, false, false, A, lda, B, ldb, 0, ep, s);
+  // Fused where the one-pass kernel takes the product with its targets: the output is
+  // neither written nor read back (a training step of 8000 cells, p = 6, 16 columns: 947
+  // -> 880 us).
+  if (wide_epi(M, N, K, false, false, lda, ldb, ep) == kWideMse)
+    return launch_gemm_bf16(M, N, K, false, false, A, lda, B, ldb, 0, ep, s);
   GemmEpi out{};
   out.bias = ep.bias;
   out.out_f32 = Y;
