@@ -1243,25 +1243,40 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   kchunk = (kchunk + kKStep - 1) / kKStep * kKStep;
   const int kz = (K + kchunk - 1) / kchunk;
   auto tiles_of = [&](int t) { return ((int64_t)N + t - 1) / t * (((int64_t)M + t - 1) / t); };
-  // Tiles of 128 once they give every CU two workgroups, tiles of 64 below that
-  // (344 x 8000 x 344: 20 us with 64, 22 with 128; 31000 columns: 38 and 33).  Long pieces of a
-  // split K range: once the pieces fill most of the CUs, as one round of 128-row tiles
-  // (131 us with pieces of 8192) then takes less than the several of the others (344 x 600
-  // x 128000, 240 tiles of 128: 146 us with 64, 131 with 128; 256 x 344 x 262144, 192: 148 and
-  // 154; 256 x 256 x 128000, 64: 70 and 130).  The pieces are the caller's: each adds its
+  // Tiles of 128 halve the LDS reads of a product, tiles of 64 give four times the
+  // workgroups, which is what counts while K is short or the tiles are few.  Measured, us
+  // with 64 and with 128: 344 x 31000, K = 128 15.8 / 17.5, 344 38 / 33; 1024 x 8192 x 344, FP32
+  // out 7 % for 128, ReLU and BF16 out 5 % against it, K = 512 17 % and 5 % for it; 1024 x
+  // 32768 x 32 32 / 34, with TB 32 / 45.  A transposed operand costs a tile of 128 more: 1024
+  // x 16384 with the mask, K = 512 13 % against 128, 1024 6 % for it.  Half a tile of rows
+  // or columns is idle below 65 (64 x 131072 x 600 40.5 / 43.7).
+  // Long pieces of a split K range: once the pieces fill most of the CUs, as one round of
+  // 128-row tiles (131 us with pieces of 8192) then takes less than the several of the
+  // others (344 x 600 x 128000, 240 tiles of 128: 146 / 131; 256 x 344 x 262144, 192: 148 /
+  // 154; 256 x 256 x 128000, 64: 70 / 130).  The pieces are the caller's: each adds its
   // FP32 sum once, so another cut would round the results differently.
-  constexpr int kFill = 512, kFillSplit = 224, kLongPiece = 4096;
+  constexpr int kFill = 480, kFillSplit = 224, kLongPiece = 4096;
   const bool far = gemm_far(ta, tb, lda, ldb, ep.kb);
-  const bool big = !far && tiles_of(128) * kz >= (split && kchunk >= kLongPiece ? kFillSplit : kFill);
+  const bool big = !far && M > 64 && N > 64 &&
+                   (split && kchunk >= kLongPiece
+                        ? tiles_of(128) * kz >= kFillSplit
+                        : tiles_of(128) * kz >= kFill && kchunk >= (ta || tb ? 1024 : ep.out_bf16 ? 448 : 320));
   const int64_t total = tiles_of(big ? 128 : 64) * kz;
   const dim3 grid((unsigned)((total + kXcds - 1) / kXcds * kXcds));
   // A long batch takes the one-pass kernel, with 128 columns per workgroup as soon
   // as that gives every CU one (256 x 32768 x 344: 26 us, tiled 30; 16384 columns:
   // 22.6 and 21.8), with 256 from twice as many on (128000 columns: 45 us, 48 with
-  // 128; 65536: 35 and 34).
+  // 128; 65536: 35 and 34).  Where its 16-row steps hold too little work for their
+  // barrier and loads, the tiled kernel (tiles of 64) stays ahead: few rows (32 x 65536 x
+  // 32: tiled 6.3, one-pass 7.0), many rows at a short K (1024 x 32768 x 32, ReLU: 27 /
+  // 30), and the mask, which a step loads just before it needs it (M x 32768, M = 256, K =
+  // 32 12 / 17, K = 256 19 / 22, K = 344 even; 65536 columns, K = 64 22 / 24, K = 128 even).
   const int epi = wide_epi(M, N, K, ta, tb, lda, ldb, ep);
   if (ep.target && epi < 0) return hipErrorInvalidValue;
-  if (epi >= 0) {
+  const bool few = M <= 32 && N < 4 * kWideMinN;
+  const bool thin = ta ? (N < 2 * kWideMinN && K <= 256) || (N < 4 * kWideMinN && K < 128)
+                       : N < 2 * kWideMinN && M >= 512 && K <= 64;
+  if (epi >= 0 && (ep.target || !(few || thin))) {
     auto wide = [&](auto ksc, auto nbc, auto tac) {
       constexpr int KS = decltype(ksc)::value, NB = decltype(nbc)::value;
       constexpr bool TA = decltype(tac)::value;
