@@ -1388,13 +1388,20 @@ hipError_t launch_cell_gather(const Operator& op, int k, const double* R, int64_
                               const double* E, int64_t lde, int Fp, uint16_t* X0t, float* Tt,
                               int64_t ldx, float* rho, int pou_sqrt, const double* dsc,
                               int blocked, hipStream_t s) {
-  // Few columns: as many cells as fill the 64 lanes, up to 8 and to 64 KiB of LDS
-  // (p = 6, 4096 cells, with E: k = 1 173 -> 55 us, k = 8 167 -> 62, k = 32 260 ->
-  // 196; p = 10, one or two cells: k = 1 298 -> 245).
+  // Few columns: several cells fill the 64 lanes, up to 8 and to 64 KiB of LDS (p = 6, 4096
+  // cells, with E: k = 1 173 -> 55 us, k = 8 167 -> 62, k = 32 260 -> 196; p = 10, one or two
+  // cells: k = 1 298 -> 245).  Every cell more lengthens a workgroup, so no more than leave
+  // the chip two workgroups per CU (k = 1, one cell and eight: p = 6, 512 cells 36.9 and 40.1,
+  // p = 2, 27 cells 6.2 and 9.1; 1000 cells, two and eight: 37.9 and 40.7); but 16 rows, which
+  // gathers of fewer pay for with their stores, where a cell has enough to store (p = 6,
+  // 512 cells: k = 4 36.8 alone, 26.1 four at a time, k = 2 37.2 and 30.5 by eight; p = 2, 27
+  // cells, k = 4 6.2 and 6.9).
   const int F = op.np * op.np * op.np;
-  int C = k < kCols ? kCols / k : 1;
-  C = std::min({C, 8, 65536 / (F * kGatherNodeBytes)});
-  if (C < 1) C = 1;
+  int most = k < kCols ? kCols / k : 1;
+  most = std::max(1, std::min({most, 8, 65536 / (F * kGatherNodeBytes)}));
+  int C = (int)std::min<int64_t>((op.ncells + 511) / 512, most);
+  const int full = (16 + k - 1) / k;  // cells of 16 rows
+  if (full <= most && F * k >= 500) C = std::max(C, full);
   dim3 grid((unsigned)((op.ncells + C - 1) / C), C > 1 ? 1 : (k + kCols - 1) / kCols);
   // One cell: LDS as if for the largest cell, six workgroups on a CU (eight of them
   // take 95 instead of 91 us at p = 2, k = 64, 13824 cells).
