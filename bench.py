@@ -85,25 +85,6 @@ def algorithmic_bytes(ndofs: int, ncells: int, p: int, q: int, nvec: int) -> int
     return 16 * ndofs * nvec + ncells * (4 * n ** 3 + 8 * m ** 3 + 48)
 
 
-def apply_kernel_name(p: int, q: int, precision: str, n=None, nvec: int = 0) -> str:
-    """The kernel the default launch shape runs.  FP64: the register-resident form where
-    the library chooses it for n cells per direction and nvec columns (cells times column
-    tiles per resident wavefront), else the box kernel, one-shot while two 8-column FP64
-    cell buffers fit 80 KiB of LDS, else persistent."""
-    if precision == "fp64" and n is not None and q <= 7 and q != 6:
-        cols = 16 if nvec > 8 else 8 if nvec > 4 else 4 if nvec > 2 else nvec
-        lx = 1 if cols >= 16 else 2 if cols == 8 else 4
-        waves = min(4, max(1, 512 // (8 * q * q + 56)))
-        steps = -(-n[0] // lx) * n[1] * n[2] * -(-nvec // cols) / (1024.0 * waves)
-        if steps >= (2 if q <= 3 else 4 if nvec % 8 and nvec > 8 else 6):
-            return "apply_pair_kernel"
-    if precision == "fp32":
-        return "apply_vec32_kernel"
-    if precision == "bf16":
-        return "apply_mixed_kernel"
-    return "apply_box_kernel" if (2 * q ** 3 * 8 + q ** 3) * 8 <= 80 * 1024 else "apply_box_pers_kernel"
-
-
 MAP_KERNEL_SOURCES = ["paper_2208_07129_amd/csrc/apply_box_map.hip", KERNEL_SOURCES[1],
                       *KERNEL_SOURCES[4:]]
 
@@ -832,8 +813,7 @@ def main(argv=None):
     achieved = flops / (kern_ms * 1e-3) / 1e12
     executed = executed_flops_per_cell_vector(w.p, w.q, box=True) * op.ncells * nvec
     traffic = traffic_for(w.name, nvec, a.precision)
-    kname = apply_kernel_name(w.p, w.q, a.precision,
-                              w.mesh.n if a.launch_cfg in (None, -1) else None, nvec)
+    kname = op.apply_kernel(nvec, a.precision)
     nbytes = algorithmic_bytes(op.ndofs, op.ncells, w.p, w.q, nvec)
     peaks = measured_peaks()
     ridge = PEAK_FP64_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)

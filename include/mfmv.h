@@ -231,6 +231,11 @@ int mf_tune(mf_operator* op, int nvec, int prec, const char* cache_path);
  * every entry -1 when the choice came from the cache).  Errors: MF_ERR_ARG. */
 int mf_tune_info(const mf_operator* op, int nvec, int prec, int* cfg, double* ms, int nms);
 
+/* The name of the fused kernel that mf_apply runs for nvec contiguous columns with
+ * this operator's launch settings (a static string; NULL on a NULL operator,
+ * nvec < 1 or a precision that is not built for the operator). */
+const char* mf_apply_kernel(const mf_operator* op, int nvec, int prec);
+
 /* Launch selection (used by the tuner and by tests):
  *   general != 0 forces the general-geometry kernel (full 3x3 factor, three
  *                LDS buffers) even on axis-aligned cells; it cannot be undone

@@ -1,4 +1,5 @@
 // C ABI of libmfmv: argument checking, operator setup and kernel dispatch.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -385,6 +386,40 @@ static bool overlaps(const void* a, size_t abytes, const void* b, size_t bbytes)
 
 }  // extern "C"
 
+namespace mf {
+
+// What an apply runs: the launch shape and, if it has items, the work split of the
+// register-resident form.  near: both multivectors' spans are below kPairMaxSpan;
+// pairs: 16-byte accesses to two columns are aligned.
+struct ApplyRoute {
+  int cfg;
+  PairPlan plan;
+};
+static ApplyRoute apply_route(const Operator& op, int nvec, int prec, bool near, bool pairs) {
+  const bool mixed = prec != MF_FP64;
+  ApplyRoute r{mixed ? op.mcfg : op.cfg, {}};
+  bool pair_asked = !mixed && r.cfg == 0;
+  if (r.cfg < 0) {
+    const auto it = op.tuned.find({prec, nvec});
+    const bool tuned = it != op.tuned.end();
+    r.cfg = tuned   ? it->second
+            : mixed ? choose_cfg_mixed(op.np, op.nq, nvec, prec)
+                    : choose_cfg_box(op.np, op.nq, nvec);
+    if (!mixed) pair_asked = tuned ? it->second == 0 : pair_chosen(op, nvec);
+  }
+  // Shape 0 is the register-resident form where it is built, its 32-bit offsets
+  // reach the multivectors and the assembly is atomic; else a box kernel shape.
+  if (pair_asked && op.box && !op.deterministic && pair_built(op.q) && near)
+    r.plan = pair_plan(op, nvec);
+  if (!pairs) {
+    if (mixed && r.cfg >= kMixedMfmaCfgs) r.cfg = vec32_cfg_single(r.cfg);
+    if (!mixed && op.box) r.cfg = box_cfg_single(op.np, op.nq, r.cfg);
+  }
+  return r;
+}
+
+}  // namespace mf
+
 int mf::apply_dispatch(mf_operator* handle, const double* X, double* Y, int nvec, int64_t ldx,
                        int64_t ldy, int prec, void* stream, bool accumulate) {
   if (!handle) return fail(MF_ERR_ARG, "operator is NULL");
@@ -419,29 +454,11 @@ int mf::apply_dispatch(mf_operator* handle, const double* X, double* Y, int nvec
   a.nvec = nvec;
   a.threads = 256;
   a.vtile = choose_vtile_f64(op->np, op->nq, nvec);
-  a.cfg = mixed ? op->mcfg : op->cfg;
-  bool pair_asked = !mixed && a.cfg == 0;
-  if (a.cfg < 0) {
-    const auto it = op->tuned.find({prec, nvec});
-    if (it != op->tuned.end())
-      a.cfg = it->second;
-    else
-      a.cfg = mixed ? choose_cfg_mixed(op->np, op->nq, nvec, prec)
-                    : choose_cfg_box(op->np, op->nq, nvec);
-    if (!mixed)
-      pair_asked = it != op->tuned.end() ? it->second == 0 : pair_chosen(*op, nvec);
-  }
-  // Shape 0 is the register-resident form where it is built, its 32-bit offsets
-  // reach the multivectors and the assembly is atomic; else a box kernel shape.
-  PairPlan plan{};
-  if (pair_asked && op->box && !op->deterministic && pair_built(op->q) &&
-      xb < (size_t)kPairMaxSpan && yb < (size_t)kPairMaxSpan)
-    plan = pair_plan(*op, nvec);
+  const ApplyRoute route = apply_route(
+      *op, nvec, prec, std::max(xb, yb) < (size_t)kPairMaxSpan, box_pairs_ok(X, Y, nvec, ldx, ldy));
+  a.cfg = route.cfg;
+  const PairPlan plan = route.plan;
   const bool pair = plan.items > 0;
-  if (mixed && a.cfg >= kMixedMfmaCfgs && !box_pairs_ok(X, Y, nvec, ldx, ldy))
-    a.cfg = vec32_cfg_single(a.cfg);
-  if (!mixed && op->box && !box_pairs_ok(X, Y, nvec, ldx, ldy))
-    a.cfg = box_cfg_single(op->np, op->nq, a.cfg);
   a.accumulate = accumulate;
 
   hipEvent_t* ev = nullptr;
@@ -497,6 +514,22 @@ int mf_apply(mf_operator* handle, const double* X, double* Y, int nvec, int64_t 
 int mf_apply_add(mf_operator* handle, const double* X, double* Y, int nvec, int64_t ldx,
                  int64_t ldy, int prec, void* stream) {
   return apply_dispatch(handle, X, Y, nvec, ldx, ldy, prec, stream, /*accumulate=*/true);
+}
+
+const char* mf_apply_kernel(const mf_operator* handle, int nvec, int prec) {
+  const Operator* op = reinterpret_cast<const Operator*>(handle);
+  if (!op || nvec < 1 || (prec != MF_FP64 && prec != MF_FP32 && prec != MF_BF16)) return nullptr;
+  const ApplyRoute r = apply_route(*op, nvec, prec,
+                                   op->ndofs * nvec < kPairMaxSpan / (int64_t)sizeof(double),
+                                   nvec % 2 == 0);
+  if (prec != MF_FP64) {
+    if (!op->box) return op->map_box && prec == MF_FP32 ? "apply_box_map_kernel" : nullptr;
+    return r.cfg >= kMixedMfmaCfgs ? "apply_vec32_kernel" : "apply_mixed_kernel";
+  }
+  if (!op->box) return op->map_box ? "apply_box_map_kernel" : "apply_f64_kernel";
+  if (r.plan.items > 0) return "apply_pair_kernel";
+  if (r.cfg == kBoxMfmaCfg) return "apply_mfma_kernel";
+  return box_cfg(op->np, op->nq, r.cfg).pers ? "apply_box_pers_kernel" : "apply_box_kernel";
 }
 
 int mf_set_launch(mf_operator* handle, int general, int cfg) {

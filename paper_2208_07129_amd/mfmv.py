@@ -32,7 +32,7 @@ EXPORTS = ("mf_num_dofs", "mf_num_cells", "mf_quad_points", "mf_constrained_mask
            "mf_apply_add", "mf_zero", "mf_set_launch", "mf_set_launch_mixed", "mf_timing",
            "mf_timing_read", "mf_timing_samples", "mf_batch_create", "mf_batch_destroy", "mf_batch_set_launch",
            "mf_batch_apply", "mf_batch_capture", "mf_batch_replay", "mf_batch_info",
-           "mf_tune", "mf_tune_info", "mf_set_deterministic", "mf_fma_probe", "mf_batch_tune", "mf_apply_batched",
+           "mf_tune", "mf_tune_info", "mf_apply_kernel", "mf_set_deterministic", "mf_fma_probe", "mf_batch_tune", "mf_apply_batched",
            "mf_last_error",
            # include/mfsolve.h
            "mf_diagonal", "mf_block_gram", "mf_block_gram_noalloc", "mf_block_gram_work",
@@ -111,6 +111,7 @@ def lib() -> ctypes.CDLL:
             "mf_batch_info": (I, [P, ctypes.POINTER(I64), ctypes.POINTER(I), ctypes.POINTER(I)]),
             "mf_tune": (I, [P, I, I, ctypes.c_char_p]),
             "mf_tune_info": (I, [P, I, I, ctypes.POINTER(I), P, I]),
+            "mf_apply_kernel": (ctypes.c_char_p, [P, I, I]),
             "mf_batch_tune": (I, [P, P, P, P, P, ctypes.c_char_p, P]),
             "mf_apply_batched": (I, [I, P, P, P, P, I, P]),
             "mf_diagonal": (I, [P, P, P]),
@@ -295,6 +296,11 @@ class Operator:
         ms = (ctypes.c_double * 16)()
         _check(lib().mf_tune_info(self._h, int(nvec), prec, ctypes.byref(cfg), ms, 16))
         return {"cfg": cfg.value, "ms": {str(i): ms[i] for i in range(16) if ms[i] >= 0}}
+
+    def apply_kernel(self, nvec: int, precision: str = "fp64") -> Optional[str]:
+        """The fused kernel that apply runs for nvec contiguous columns (mf_apply_kernel)."""
+        name = lib().mf_apply_kernel(self._h, int(nvec), PRECISIONS[precision])
+        return name.decode() if name else None
 
     def set_launch_mixed(self, cfg: int = -1):
         _check(lib().mf_set_launch_mixed(self._h, int(cfg)))
