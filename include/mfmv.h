@@ -231,10 +231,11 @@ int mf_tune(mf_operator* op, int nvec, int prec, const char* cache_path);
  * every entry -1 when the choice came from the cache).  Errors: MF_ERR_ARG. */
 int mf_tune_info(const mf_operator* op, int nvec, int prec, int* cfg, double* ms, int nms);
 
-/* The name of the fused kernel that mf_apply runs for nvec contiguous columns with
- * this operator's launch settings (a static string; NULL on a NULL operator,
- * nvec < 1 or a precision that is not built for the operator). */
-const char* mf_apply_kernel(const mf_operator* op, int nvec, int prec);
+/* The name of the fused kernel that mf_apply (mf_apply_add with accumulate != 0)
+ * runs for nvec contiguous columns with this operator's launch settings (a static
+ * string; NULL on a NULL operator, nvec < 1 or a precision that is not built for
+ * the operator). */
+const char* mf_apply_kernel(const mf_operator* op, int nvec, int prec, int accumulate);
 
 /* Launch selection (used by the tuner and by tests):
  *   general != 0 forces the general-geometry kernel (full 3x3 factor, three
@@ -243,9 +244,10 @@ const char* mf_apply_kernel(const mf_operator* op, int nvec, int prec);
  *   cfg          launch shape of the axis-aligned-cell kernel, 0..12, or -1
  *                for the built-in choice by column count and mesh.  Shape 0
  *                holds a cell of up to 16 columns in the registers of one
- *                wavefront that marches along y (q <= 7; other calls, and
- *                multivectors that span 3.75 GiB or more or a deterministic
- *                assembly, run the box kernel's default shape instead).
+ *                wavefront that marches along y (q <= 7, mf_apply_add q <= 3;
+ *                other calls, and multivectors that span 3.75 GiB or more or a
+ *                deterministic assembly, run the box kernel's default shape
+ *                instead).
  *                Shapes 2 and 4 give
  *                every thread two adjacent columns (16-byte accesses); a call
  *                with odd nvec, odd ldx or ldy, or X or Y not 16-byte aligned

@@ -191,7 +191,11 @@ apply_pair_kernel(const GridDesc grid, const double* __restrict__ geo,
 template <int NP, int NQ, int B>
 hipError_t launch_pair(const ApplyLaunch& a, const PairPlan& plan, hipStream_t s) {
   const auto span = [&](int64_t ld) { return (uint32_t)((((int64_t)a.grid.N[0] * a.grid.N[1] * a.grid.N[2] - 1) * ld + a.nvec) * 8); };
-  auto k = a.accumulate ? apply_pair_kernel<NP, NQ, B, true> : apply_pair_kernel<NP, NQ, B, false>;
+  auto k = apply_pair_kernel<NP, NQ, B, false>;
+  if (a.accumulate) {
+    if constexpr (NQ <= kPairAccumMaxQ) k = apply_pair_kernel<NP, NQ, B, true>;
+    else return hipErrorInvalidValue;
+  }
   hipLaunchKernelGGL(k, dim3((unsigned)(plan.chunk * kXcds)), dim3(64), 0, s, a.grid, a.geo, a.vq,
                      a.X, a.Y, (uint32_t)a.ldx, (uint32_t)a.ldy, a.nvec, plan, span(a.ldx),
                      span(a.ldy));

@@ -395,21 +395,24 @@ struct ApplyRoute {
   int cfg;
   PairPlan plan;
 };
-static ApplyRoute apply_route(const Operator& op, int nvec, int prec, bool near, bool pairs) {
+static ApplyRoute apply_route(const Operator& op, int nvec, int prec, bool accumulate, bool near,
+                              bool pairs) {
   const bool mixed = prec != MF_FP64;
   ApplyRoute r{mixed ? op.mcfg : op.cfg, {}};
   bool pair_asked = !mixed && r.cfg == 0;
   if (r.cfg < 0) {
     const auto it = op.tuned.find({prec, nvec});
-    const bool tuned = it != op.tuned.end();
+    // the tuner times the storing form, whose shape 0 is another kernel than the accumulating one's
+    const bool tuned =
+        it != op.tuned.end() && !(accumulate && !mixed && it->second == 0);
     r.cfg = tuned   ? it->second
             : mixed ? choose_cfg_mixed(op.np, op.nq, nvec, prec)
                     : choose_cfg_box(op.np, op.nq, nvec);
-    if (!mixed) pair_asked = tuned ? it->second == 0 : pair_chosen(op, nvec);
+    if (!mixed) pair_asked = tuned ? it->second == 0 : pair_chosen(op, nvec, accumulate);
   }
   // Shape 0 is the register-resident form where it is built, its 32-bit offsets
   // reach the multivectors and the assembly is atomic; else a box kernel shape.
-  if (pair_asked && op.box && !op.deterministic && pair_built(op.q) && near)
+  if (pair_asked && op.box && !op.deterministic && pair_built(op.q, accumulate) && near)
     r.plan = pair_plan(op, nvec);
   if (!pairs) {
     if (mixed && r.cfg >= kMixedMfmaCfgs) r.cfg = vec32_cfg_single(r.cfg);
@@ -455,7 +458,8 @@ int mf::apply_dispatch(mf_operator* handle, const double* X, double* Y, int nvec
   a.threads = 256;
   a.vtile = choose_vtile_f64(op->np, op->nq, nvec);
   const ApplyRoute route = apply_route(
-      *op, nvec, prec, std::max(xb, yb) < (size_t)kPairMaxSpan, box_pairs_ok(X, Y, nvec, ldx, ldy));
+      *op, nvec, prec, accumulate, std::max(xb, yb) < (size_t)kPairMaxSpan,
+      box_pairs_ok(X, Y, nvec, ldx, ldy));
   a.cfg = route.cfg;
   const PairPlan plan = route.plan;
   const bool pair = plan.items > 0;
@@ -516,10 +520,10 @@ int mf_apply_add(mf_operator* handle, const double* X, double* Y, int nvec, int6
   return apply_dispatch(handle, X, Y, nvec, ldx, ldy, prec, stream, /*accumulate=*/true);
 }
 
-const char* mf_apply_kernel(const mf_operator* handle, int nvec, int prec) {
+const char* mf_apply_kernel(const mf_operator* handle, int nvec, int prec, int accumulate) {
   const Operator* op = reinterpret_cast<const Operator*>(handle);
   if (!op || nvec < 1 || (prec != MF_FP64 && prec != MF_FP32 && prec != MF_BF16)) return nullptr;
-  const ApplyRoute r = apply_route(*op, nvec, prec,
+  const ApplyRoute r = apply_route(*op, nvec, prec, accumulate != 0,
                                    op->ndofs * nvec < kPairMaxSpan / (int64_t)sizeof(double),
                                    nvec % 2 == 0);
   if (prec != MF_FP64) {

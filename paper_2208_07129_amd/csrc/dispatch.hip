@@ -477,7 +477,12 @@ hipError_t launch_apply_box(const Operator& op, const ApplyLaunch& a, hipStream_
   }
 }
 
-bool pair_built(int q) { return q <= 7; }
+// The accumulating form is built for at most three points per direction: its read of
+// a stored row waits for the additions issued before it, which more points cost more
+// than the form gains (box kernel against this, us: p = 6, 16^3, 64 columns 563 / 768,
+// 16 columns 112 / 152; p = 4, 24^3, 64 columns 550 / 698; p = 3, 20^3, 24 columns -25 %;
+// p = 2, 32^3, 64 columns 405 / 252, one column 41 / 27; p = 1, 40^3, 16 columns 66 / 56).
+bool pair_built(int q, bool accumulate) { return q <= (accumulate ? kPairAccumMaxQ : 7); }
 
 // Where the register-resident apply is the built-in choice: at most seven points per
 // direction, and enough cells for its one or two wavefronts per SIMD to run
@@ -490,8 +495,8 @@ bool pair_built(int q) { return q <= 7; }
 // against 151); p = 2, 32^3, 2 (one column) 32 against 75.  Six points have
 // three pairs for four lane groups and do not win (p = 5, 14^3, 64 columns: 218
 // against 215 us).
-bool pair_chosen(const Operator& op, int nvec) {
-  if (op.nq > 7 || op.nq == 6) return false;
+bool pair_chosen(const Operator& op, int nvec, bool accumulate) {
+  if (!pair_built(op.nq, accumulate) || op.nq == 6) return false;
   const int cols = pair_columns(nvec), lx = pair_cells(cols);
   const double steps = (double)((op.grid.n[0] + lx - 1) / lx) * op.grid.n[1] * op.grid.n[2] *
                        ((nvec + cols - 1) / cols) / (1024.0 * pair_waves(op.nq));

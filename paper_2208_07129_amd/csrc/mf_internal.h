@@ -259,8 +259,8 @@ hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int
 hipError_t launch_apply_box(const Operator& op, const ApplyLaunch& a, hipStream_t s);
 // Register-resident form of the same (q <= 7, spans below kPairMaxSpan bytes).
 constexpr int64_t kPairMaxSpan = 0xF0000000LL;
-bool pair_built(int q);
-bool pair_chosen(const Operator& op, int nvec);
+bool pair_built(int q, bool accumulate);
+bool pair_chosen(const Operator& op, int nvec, bool accumulate);
 PairPlan pair_plan(const Operator& op, int nvec, int cols = 0);  // cols 0: by nvec
 // Its Chebyshev step: no items where it is not taken; span: bytes of a multivector.
 PairPlan cheb_pair_plan(const Operator& op, int nvec, int64_t span);

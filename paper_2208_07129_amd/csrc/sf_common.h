@@ -538,6 +538,7 @@ constexpr int pair_cells(int B) { return B >= 16 ? 1 : B == 8 ? 2 : 4; }
 constexpr int pair_columns(int nvec) {
   return nvec > 8 ? 16 : nvec > 4 ? 8 : nvec > 2 ? 4 : nvec;
 }
+constexpr int kPairAccumMaxQ = 3;  // points up to which the accumulating form is built
 template <int P>
 hipError_t launch_cheb_pair_p(const Operator& op, const double* Y, double* Out, int64_t ld,
                               int nvec, const ChebArgs& ca, const PairPlan& plan, hipStream_t s);

@@ -111,7 +111,7 @@ def lib() -> ctypes.CDLL:
             "mf_batch_info": (I, [P, ctypes.POINTER(I64), ctypes.POINTER(I), ctypes.POINTER(I)]),
             "mf_tune": (I, [P, I, I, ctypes.c_char_p]),
             "mf_tune_info": (I, [P, I, I, ctypes.POINTER(I), P, I]),
-            "mf_apply_kernel": (ctypes.c_char_p, [P, I, I]),
+            "mf_apply_kernel": (ctypes.c_char_p, [P, I, I, I]),
             "mf_batch_tune": (I, [P, P, P, P, P, ctypes.c_char_p, P]),
             "mf_apply_batched": (I, [I, P, P, P, P, I, P]),
             "mf_diagonal": (I, [P, P, P]),
@@ -297,9 +297,10 @@ class Operator:
         _check(lib().mf_tune_info(self._h, int(nvec), prec, ctypes.byref(cfg), ms, 16))
         return {"cfg": cfg.value, "ms": {str(i): ms[i] for i in range(16) if ms[i] >= 0}}
 
-    def apply_kernel(self, nvec: int, precision: str = "fp64") -> Optional[str]:
+    def apply_kernel(self, nvec: int, precision: str = "fp64",
+                     accumulate: bool = False) -> Optional[str]:
         """The fused kernel that apply runs for nvec contiguous columns (mf_apply_kernel)."""
-        name = lib().mf_apply_kernel(self._h, int(nvec), PRECISIONS[precision])
+        name = lib().mf_apply_kernel(self._h, int(nvec), PRECISIONS[precision], int(accumulate))
         return name.decode() if name else None
 
     def set_launch_mixed(self, cfg: int = -1):

@@ -1,9 +1,12 @@
 """mf_apply_kernel names the kernel that an apply runs: with the built-in choice, a launch
 shape, the deterministic assembly, spans past 32-bit offsets, and on general cells."""
+import numpy as np
 import pytest
 
 import workloads as W
 from paper_2208_07129_amd import mfmv
+
+from test_gpu_apply import build_pair, colrel, TOL
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -41,4 +44,37 @@ def test_kernel_names():
     assert sheared.apply_kernel(4) == "apply_f64_kernel"
     assert sheared.apply_kernel(4, "fp32") is None
     assert op.apply_kernel(0) is None
-    assert mfmv.lib().mf_apply_kernel(None, 4, 0) is None
+    assert mfmv.lib().mf_apply_kernel(None, 4, 0, 0) is None
+
+
+def test_accumulating_apply():
+    """More than three points per direction accumulate in the box kernel, whatever the
+    storing form runs: by choice, by shape and after tuning."""
+    for p, q, n, k in [(6, 7, 12, 64), (4, 5, 16, 64), (3, 4, 20, 32), (2, 4, 16, 33)]:
+        op = cube(n, p, q)
+        assert op.apply_kernel(k, accumulate=True) == BOX
+        op.set_launch(False, 0)
+        assert op.apply_kernel(k) == PAIR and op.apply_kernel(k, accumulate=True) == BOX
+    for p, q, n, k in [(2, 3, 32, 1), (2, 3, 24, 64), (1, 3, 40, 16), (1, 2, 40, 4)]:
+        assert cube(n, p, q).apply_kernel(k, accumulate=True) == PAIR
+    op = cube(12, 4)
+    op.set_launch(False, 0)
+    op.tune(33)
+    assert op.apply_kernel(33, accumulate=True) == BOX
+
+
+@pytest.mark.parametrize("p,q,n,k", [(6, 7, (4, 5, 3), 33), (4, 5, (5, 4, 4), 64), (3, 4, (4, 6, 5), 17),
+                                     (2, 4, (6, 5, 7), 9), (2, 3, (16, 17, 18), 33),
+                                     (1, 3, (20, 20, 21), 20), (2, 3, (33, 16, 16), 1)])
+def test_accumulating_apply_matches_the_oracle(p, q, n, k):
+    mesh = W.BoxMesh(n=n, bc=W.BC_DIRICHLET0)
+    op, orc = build_pair(mesh, p, q)
+    rng = np.random.default_rng(p + k)
+    X, Y0 = rng.uniform(-1, 1, (orc.ndofs, k)), rng.uniform(-1, 1, (orc.ndofs, k))
+    ref = Y0 + orc.apply(X)
+    ref[orc.constrained] = Y0[orc.constrained]
+    for shape in (-1, 0):
+        op.set_launch(False, shape)
+        Y = torch.from_numpy(Y0).to("cuda")
+        op.apply(torch.from_numpy(X).to("cuda"), Y, accumulate=True)
+        assert colrel(Y.cpu().numpy(), ref) <= TOL
