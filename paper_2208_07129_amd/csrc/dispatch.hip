@@ -484,23 +484,77 @@ hipError_t launch_apply_box(const Operator& op, const ApplyLaunch& a, hipStream_
 // p = 2, 32^3, 64 columns 405 / 252, one column 41 / 27; p = 1, 40^3, 16 columns 66 / 56).
 bool pair_built(int q, bool accumulate) { return q <= (accumulate ? kPairAccumMaxQ : 7); }
 
-// Where the register-resident apply is the built-in choice: at most seven points per
-// direction, and enough cells for its one or two wavefronts per SIMD to run
-// several each (a single cell takes a wavefront some 15 us, so on small
-// multivectors the box kernel's many short workgroups finish first).  Measured
-// at cells-times-tiles per resident wavefront: p = 6, 16^3 cells, 4 (16 columns)
-// 128 against 117 us, 8 (32) 224 against 257, 16 (64) 415 against 506; p = 4, 24^3,
-// 3.4 (8 columns) 85 against 86, 6.8 (16) 132 against 158; column counts that leave
-// part of the box kernel's tiles idle win earlier (p = 6, 12 columns, 4: 135
-// against 151); p = 2, 32^3, 2 (one column) 32 against 75.  Six points have
-// three pairs for four lane groups and do not win (p = 5, 14^3, 64 columns: 218
-// against 215 us).
+// Work of the register-resident form: cells (groups of cells in x) times column tiles per
+// resident wavefront.
+static double pair_steps(const Operator& op, int nvec, int cols) {
+  const int lx = pair_cells(cols);
+  return (double)((op.grid.n[0] + lx - 1) / lx) * op.grid.n[1] * op.grid.n[2] *
+         ((nvec + cols - 1) / cols) / (1024.0 * pair_waves(op.nq));
+}
+
+// The steps (pair_steps) from which the register-resident apply is the faster one, < 0 where
+// it never is.  A cell takes a wavefront some 15 us, so small multivectors need the box
+// kernel's many short workgroups, and a tile of 16 columns costs the same when half of it
+// is idle, where the box kernel has tiles of 8.  Box kernel against this, us or the ratio
+// of the two, at the steps given:
+//  1, 2 columns: the box kernel assembles along rows there; p = 2, 32^3 (2.0) 1.44 and 1.09, p = 1,
+//    40^3 (3.9) 1.58; more than three points 0.5 to 0.87 at up to 16 steps.
+//  3, 4: three points 1.4 to 2; four 0.95 (3.5), 1.06 to 1.17 (7.8); five 0.92 to 0.97 (p = 2 1.6);
+//    seven 0.85 to 0.94.
+//  5 to 7: four and more points 1.04 to 1.36 from 6 steps on.  8, no idle slots in the box
+//    kernel: three points 0.98 (1.7), 1.05 (4.0), 1.35 (13.5); five, p < 4, 1.08 to 1.23; else 0.89 to
+//    1.05.
+//  More, the last tile filled (k mod 16 = 9 to 15): from 2 steps on at up to three points, 4
+//    above.  k mod 16 = 0: three points from 2; four and five 6 (p = 4, 24^3, 6.8 158 / 132, p = 3,
+//    20^3, 32 columns, 7.8 1.10); seven 7 (p = 6, 12^3, 6.8 0.99; 16^3, 16 columns, 4 117 / 122, 32, 8 1.15).
+//  The last tile at most half filled: 24 columns 0.92 to 0.99 with four, with five at p = 3 and with
+//    seven points, 1.0 to 1.2 with three and with five else; 17 to 23 not for seven points (p =
+//    4 0.93, p = 6, 20 columns 0.94); 40, 56 and so on 1.05 to 1.3 from 7 steps on, seven points from
+//    14 (p = 6: 0.94 at 6.8, 0.99 at 12, 1.06 at 16).
+//  Two points (p = 1): whole tiles from 12 steps (1.06 to 1.17; 0.98 at 6), half tiles of 40 and
+//    more columns from 30 (1.06 to 1.17; 0.84 at 6, 0.97 at 21), 8 and 24 columns 0.79 to 1.06; on
+//    meshes of few cells in x none of these (7 x 64 x 64: 16 columns 0.93, 20 0.94, 56 0.89; the
+//    others there 1.2 to 1.4).
+//  Four points at p < 3: with idle slots in the box kernel (p = 2, 40^3: 9 columns 1.45; 24 0.81),
+//    whole tiles from 60 steps (1.04 to 1.11; 28^3, 16 columns, 10.7 0.91, 64, 43 0.98); p = 1: 3 and 4
+//    columns 2.4, others 0.75 to 1.02.
+//  Six points: three pairs for four lane groups, 0.9 to 1.1.
+static double pair_least_steps(const Operator& op, int nvec) {
+  const int p = op.p, nq = op.nq, rem = nvec % 16;
+  if (nq > 7 || nq == 6) return -1.0;
+  if (nvec <= 2) return nq <= 3 ? 2.0 : -1.0;
+  if (nvec <= 4) return nq <= 3 ? 2.0 : nq == 4 || (nq == 5 && p == 2) ? 6.0 : -1.0;
+  if (nq == 4 && p == 1) return -1.0;
+  if (nvec < 8) return nq <= 3 ? 2.0 : 6.0;
+  if (nvec == 8) return nq == 3 ? 4.0 : nq == 5 && p < 4 ? 6.0 : -1.0;
+  const bool half = rem >= 1 && rem <= 8;  // idle half of the last tile
+  if (nq == 2) {
+    if ((nvec % 8 == 0 || (half && nvec % 4 == 0)) && op.grid.n[0] < 16) return -1.0;
+    if (nvec % 8 == 0) return rem == 0 ? 12.0 : nvec >= 40 ? 30.0 : -1.0;
+    return 2.0;
+  }
+  if (nq == 4 && p == 2)
+    return rem == 0 ? 60.0 : nvec % 8 == 0 || (half && nvec < 32) ? -1.0 : 6.0;
+  if (rem == 8) {
+    if (nvec == 24) return nq == 3 || (nq == 5 && p != 3) ? 6.0 : -1.0;
+    return nq == 3 ? 4.0 : nq == 7 ? 14.0 : 7.0;
+  }
+  if (half && nvec % 4 == 0)
+    return nq == 7 && nvec < 32 ? -1.0 : nq <= 3 || (nq == 5 && p == 4) ? 4.0 : 7.0;
+  if (half) return nq == 7 && p == 4 && nvec < 32 ? -1.0 : nq <= 3 ? 2.0 : 4.0;
+  if (rem == 0) return nq == 3 ? 2.0 : nq == 7 ? 7.0 : 6.0;
+  return nq <= 3 ? 2.0 : 4.0;
+}
+
+// Whether the register-resident apply is the built-in choice.  Accumulating, whole and half
+// tiles gain less (p = 2: 8 columns 0.97 at 4 steps, 1.16 at 13.5; 24 columns 0.95 at 6.8, 1.03 at 16; 40
+// 1.18 at 24).
 bool pair_chosen(const Operator& op, int nvec, bool accumulate) {
-  if (!pair_built(op.nq, accumulate) || op.nq == 6) return false;
-  const int cols = pair_columns(nvec), lx = pair_cells(cols);
-  const double steps = (double)((op.grid.n[0] + lx - 1) / lx) * op.grid.n[1] * op.grid.n[2] *
-                       ((nvec + cols - 1) / cols) / (1024.0 * pair_waves(op.nq));
-  return steps >= (op.nq <= 3 ? 2.0 : nvec % 8 != 0 && nvec > 8 ? 4.0 : 6.0);
+  if (!pair_built(op.nq, accumulate)) return false;
+  double least = pair_least_steps(op, nvec);
+  if (least < 0.0) return false;
+  if (accumulate && nvec % 16 == 8) least = std::max(least, 12.0);
+  return pair_steps(op, nvec, pair_columns(nvec)) >= least;
 }
 
 // The columns per wavefront and the segment length of the register-resident

@@ -78,3 +78,27 @@ def test_accumulating_apply_matches_the_oracle(p, q, n, k):
         Y = torch.from_numpy(Y0).to("cuda")
         op.apply(torch.from_numpy(X).to("cuda"), Y, accumulate=True)
         assert colrel(Y.cpu().numpy(), ref) <= TOL
+
+
+@pytest.mark.parametrize("p,q,n,pair,box", [
+    # (columns of the register form, columns of the box kernel)
+    (6, 7, 16, (9, 12, 32, 33, 64), (1, 2, 4, 8, 16, 24, 40)),
+    (6, 7, 12, (33, 128), (1, 8, 40, 56, 64)),
+    (4, 5, 24, (9, 16, 20, 24, 32, 64), (1, 2, 4, 8)),
+    (3, 4, 20, (17, 20, 32, 40, 64), (1, 2, 8, 9, 16, 24)),
+    (2, 3, 32, (1, 2, 4, 8, 16, 24, 64), ()),
+    (2, 3, 8, (), (1, 2, 4, 8, 16, 24, 64)),
+    (2, 4, 16, (33,), (1, 8, 16, 20, 24, 40, 64)),
+    (1, 2, 40, (1, 4, 9, 16, 20, 32), (8, 24)),
+    (1, 2, (7, 64, 64), (1, 4, 9, 12), (8, 16, 20, 24, 56, 64)),
+    (1, 4, 40, (3, 4), (1, 8, 12, 16, 24, 64)),
+    (5, 6, 20, (), (1, 9, 16, 64)),
+    (8, 9, 12, (), (1, 8, 64)),
+])
+def test_choice_between_register_form_and_box_kernel(p, q, n, pair, box):
+    """Narrow blocks, half-idle tiles and points per direction on both sides of the rule."""
+    op = cube(n, p, q)
+    for k in pair:
+        assert op.apply_kernel(k) == PAIR, k
+    for k in box:
+        assert op.apply_kernel(k) in (BOX, PERS), k
