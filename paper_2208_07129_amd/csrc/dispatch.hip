@@ -548,20 +548,24 @@ static double pair_least_steps(const Operator& op, int nvec) {
 
 // Whether the register-resident apply is the built-in choice.  Accumulating, whole and half
 // tiles gain less (p = 2: 8 columns 0.97 at 4 steps, 1.16 at 13.5; 24 columns 0.95 at 6.8, 1.03 at 16; 40
-// 1.18 at 24).
+// 1.18 at 24), and a mesh with fewer cells in x than share a wavefront loses (p = 2, 1 x 30000
+// x 1, one column 42 / 81 us).
 bool pair_chosen(const Operator& op, int nvec, bool accumulate) {
   if (!pair_built(op.nq, accumulate)) return false;
   double least = pair_least_steps(op, nvec);
   if (least < 0.0) return false;
+  const int cols = pair_columns(nvec);
+  if (accumulate && op.grid.n[0] < pair_cells(cols)) return false;
   if (accumulate && nvec % 16 == 8) least = std::max(least, 12.0);
-  return pair_steps(op, nvec, pair_columns(nvec)) >= least;
+  return pair_steps(op, nvec, cols) >= least;
 }
 
 // The columns per wavefront and the segment length of the register-resident
 // apply.  Segments: shorter ones give more wavefronts, longer ones share more
 // rows between consecutive cells, and a wavefront's first cell has nothing to
 // hide its loads behind; the estimate is rounds of resident wavefronts times
-// (cells of a segment + that start).
+// (cells of a segment + that start).  Only the fewest segments of each length are
+// looked at, some 2 sqrt(ny) of them: the plan is made on every call.
 PairPlan pair_plan(const Operator& op, int nvec, int cols) {
   PairPlan b{};
   b.cols = cols > 0 ? cols : pair_columns(nvec);
@@ -571,9 +575,8 @@ PairPlan pair_plan(const Operator& op, int nvec, int cols) {
   const int64_t lines = (int64_t)b.nxg * op.grid.n[2] * b.ntiles, ny = op.grid.n[1];
   const double slots = 1024.0 * pair_waves(op.nq);
   double best = 0.0;
-  for (int64_t nseg = 1; nseg <= ny; ++nseg) {
-    const int64_t len = (ny + nseg - 1) / nseg;
-    if ((ny + len - 1) / len != nseg) continue;
+  for (int64_t nseg = 1, len = ny;; nseg = (ny + len - 2) / (len - 1)) {
+    len = (ny + nseg - 1) / nseg;
     const double r = (double)(lines * nseg) / slots;
     const double rounds = r < 4.0 ? (double)(int64_t)(r + 0.999999) : r + 0.5;
     const double cost = rounds * ((double)len + 0.5);  // p = 6, 16^3, 64 columns: 406 us in one
@@ -583,6 +586,7 @@ PairPlan pair_plan(const Operator& op, int nvec, int cols) {
       b.len = (int)len;
       b.nseg = (int)nseg;
     }
+    if (len == 1) break;
   }
   const int64_t items = lines * b.nseg;
   b.items = items < (1LL << 30) ? (int)items : 0;
@@ -602,13 +606,11 @@ PairPlan cheb_pair_plan(const Operator& op, int nvec, int64_t span) {
   if (op.nq > 7 || op.deterministic || op.cfg > 0 || span >= kPairMaxSpan ||
       op.ndofs * 8 >= kPairMaxSpan)
     return PairPlan{};
-  const PairPlan plan = pair_plan(op, nvec, 16);
-  if (op.cfg == 0) return plan;
-  const double steps = (double)op.ncells * plan.ntiles / (1024.0 * pair_waves(op.nq));
   const double least = op.nq <= 3   ? 2.0
                        : op.nq == 7 ? 4.0
                        : op.nq == 5 || (op.nq == 4 && nvec % 8 != 0) ? 6.0 : 10.0;
-  return nvec > 8 && steps >= least ? plan : PairPlan{};
+  const bool chosen = op.cfg == 0 || (nvec > 8 && pair_steps(op, nvec, 16) >= least);
+  return chosen ? pair_plan(op, nvec, 16) : PairPlan{};
 }
 
 hipError_t launch_cheb_pair(const Operator& op, const double* Y, double* Out, int64_t ld, int nvec,

@@ -57,6 +57,8 @@ def test_accumulating_apply():
         assert op.apply_kernel(k) == PAIR and op.apply_kernel(k, accumulate=True) == BOX
     for p, q, n, k in [(2, 3, 32, 1), (2, 3, 24, 64), (1, 3, 40, 16), (1, 2, 40, 4)]:
         assert cube(n, p, q).apply_kernel(k, accumulate=True) == PAIR
+    op = cube((1, 30000, 1), 2)  # fewer cells in x than share a wavefront
+    assert op.apply_kernel(1) == PAIR and op.apply_kernel(1, accumulate=True) == BOX
     op = cube(12, 4)
     op.set_launch(False, 0)
     op.tune(33)
