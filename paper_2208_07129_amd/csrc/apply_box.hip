@@ -61,9 +61,13 @@ hipError_t launch_box(const ApplyLaunch& a, hipStream_t s) {
   // item, so tiles of four columns and cells of nine points take it only on meshes
   // that fill the chip.  Without and with it, one column: p = 6, 16^3 72 / 47 us, 6^3
   // 20 / 18, 4^3 15.3 / 16.1; p = 8, 12^3 62 / 43, 4^3 19 / 20; two: p = 8, 12^3 62 / 54, 4^3 19 / 22;
-  // four: p = 6, 16^3 75 / 69, 6^3 19 / 20; p = 4, 24^3 93 / 85; p = 8, 12^3 70 / 78.
-  constexpr bool rows_built = !PERS && C == 1 && B <= (NP >= 9 ? 2 : 4);
-  constexpr int64_t rows_min = B <= 2 && NP <= 8 ? 128 : 1024;
+  // four: p = 6, 16^3 75 / 69, 6^3 19 / 20; p = 4, 24^3 93 / 85; p = 8, 12^3 70 / 78; p = 1, 40^3
+  // 85 / 87.  Accumulating, its read of the stored rows stands among the additions: p =
+  // 6, 10^3, one column 19.5 / 16.7, two 21.0 / 18.2, 6^3 9.1 / 9.9 and 9.2 / 9.8; four: 16^3
+  // 60.2 / 62.0, p = 7, 12^3 45 / 49, and at most 1.2 for it (p = 3, 20^3 32 / 27), not taken.
+  constexpr int rows_max = ACCUM && NP >= 10 ? 1 : NP >= 9 || NP <= 2 || ACCUM ? 2 : 4;
+  constexpr bool rows_built = !PERS && C == 1 && B <= rows_max;
+  constexpr int64_t rows_min = B <= 2 && NP <= 8 && !ACCUM ? 128 : 1000;
   Kern k;
   if constexpr (PERS) k = apply_box_pers_kernel<NP, NQ, B, C, NT, ACCUM>;
   else k = apply_box_kernel<NP, NQ, B, C, NT, ACCUM, false>;
