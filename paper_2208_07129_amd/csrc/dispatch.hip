@@ -594,22 +594,48 @@ PairPlan pair_plan(const Operator& op, int nvec, int cols) {
   return b;
 }
 
-// The Chebyshev step in the register-resident form: asked for (shape 0), or the
-// built-in choice where it wins.  Measured with the initialisation, box kernel
-// against this, at cells-times-tiles per resident wavefront: p = 6, 16^3 cells, 16
-// columns (4) 206 against 186 us, 64 (16) 801 / 557, 8^3 cells, 64 (2) 97 / 100;
-// p = 4, 24^3, 16 (6.8) 242 / 237, 64 (27) 898 / 677, 10^3, 128 (3.9) 109 / 124; p = 3,
-// 24^3, 12 (6.8) 140 / 127, 16 (6.8) 121 / 128, 32 (13.5) 197 / 188; q = 6: 14^3, 16
-// (2.7) 95 / 101, 64 (10.7) 316 / 296; p = 2, 32^3, 8 88 / 107, 16 (8) 129 / 113, 16^3,
-// 16 (1) 33 / 34, 64 (4) 66 / 58.
+// The steps from which the Chebyshev step is faster in the register-resident form, < 0 where
+// it never is.  Measured with the initialisation, time of the box kernel over this one's, at the
+// steps given:
+//  k <= 8: half of the 16 columns idle, not taken.  k mod 16 = 9 to 15 and whole tiles: three
+//    points from 2 (p = 2, 16^3, 32 columns, 2 1.19); seven from 4 (p = 6, 16^3, 16, 4 1.15; 12^3, 1.7
+//    0.98); five from 6 (p = 4, 24^3, 16, 6.8 1.08; 16^3, 2 0.86); four at p = 3 from 10, with idle
+//    slots in the box kernel's tiles from 6 (16^3, 48 columns, 6 0.92, 20^3, 11.7 1.04; 36, 6 1.09); six from
+//    10 (p = 5, 20^3, 16, 7.8 1.05; 14^3, 2.7 0.92); two from 12 (p = 1, 40^3 1.08; 20^3, 7.8 0.98).
+//  24 columns (a quarter of two tiles idle): three and five points from 12 (p = 2, 24^3, 6.8 0.98; p =
+//    3, q = 5, 28^3, 21 1.06, 20^3, 7.8 0.91), seven from 8 (p = 6, 16^3 1.07; p = 4, 14^3, 5.4 0.92); others
+//    0.76 to 0.93.  17 to 23: not with six points (p = 3 0.90 to 0.92, p = 4 0.91), seven from 8.
+//  40, 56 and so on: three points from 2, five from 7 (p = 4, 16^3, 6 0.88, 8 1.08), seven from 8 (p = 5, 12^3,
+//    5.1 0.98), four at p = 3 from 15 (20^3, 11.7 0.95, 15.6 1.00), six from 12 (p = 4, 14^3, 10.7 0.88); two
+//    points 0.78 to 1.17, not taken.
+//  Four points at p < 3: p = 2 with idle slots in the box kernel's tiles from 10 (28^3, 9 columns 1.13),
+//    whole tiles of 48 and more columns from 30 (48, 32 1.01; 64, 43 1.05; 32, 21 0.94); p = 1 0.78 to 1.05.
+static double cheb_least_steps(int p, int nq, int nvec) {
+  const int rem = nvec % 16;
+  const bool half = rem >= 1 && rem <= 8;
+  if (nvec <= 8 || nq > 7 || (nq == 4 && p == 1)) return -1.0;
+  if (nq == 4 && p == 2) {
+    if (rem == 0) return nvec >= 48 ? 30.0 : -1.0;
+    return nvec % 8 == 0 || (half && nvec < 32) ? -1.0 : 10.0;
+  }
+  if (half && nvec <= 24) {
+    if (nq == 6 || (nvec == 24 && (nq == 2 || nq == 4))) return -1.0;
+    if (nq == 7) return 8.0;
+    if (nvec == 24) return 12.0;
+  }
+  if (nq == 2) return rem == 8 ? -1.0 : 12.0;
+  if (nq == 3) return 2.0;
+  if (nq == 7) return half && nvec % 4 == 0 ? 8.0 : 4.0;
+  if (nq == 6) return half ? 12.0 : 10.0;
+  if (nq == 5) return rem == 8 ? 7.0 : 6.0;
+  return rem == 8 ? 15.0 : rem == 0 ? 10.0 : 6.0;
+}
 PairPlan cheb_pair_plan(const Operator& op, int nvec, int64_t span) {
   if (op.nq > 7 || op.deterministic || op.cfg > 0 || span >= kPairMaxSpan ||
       op.ndofs * 8 >= kPairMaxSpan)
     return PairPlan{};
-  const double least = op.nq <= 3   ? 2.0
-                       : op.nq == 7 ? 4.0
-                       : op.nq == 5 || (op.nq == 4 && nvec % 8 != 0) ? 6.0 : 10.0;
-  const bool chosen = op.cfg == 0 || (nvec > 8 && pair_steps(op, nvec, 16) >= least);
+  const double least = cheb_least_steps(op.p, op.nq, nvec);
+  const bool chosen = op.cfg == 0 || (least > 0.0 && pair_steps(op, nvec, 16) >= least);
   return chosen ? pair_plan(op, nvec, 16) : PairPlan{};
 }
 
