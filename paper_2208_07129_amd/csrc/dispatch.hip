@@ -249,8 +249,9 @@ hipError_t launch_zero_shared_rows(double* Y, const int64_t nodes[3], int p, int
   if (wgs > lines) wgs = lines;
   // Lines of few elements go to single wavefronts, a line or a few each: with a
   // workgroup per line most of its threads have no row (one column, between events: p = 6,
-  // 16^3 12.9 -> 7.2 us, 30^3 23 -> 13; four columns, 16^3 10.8 -> 8.0).
-  const bool narrow = nodes[0] << cw_log2 <= kNarrowLine;
+  // 16^3 12.9 -> 7.2 us, 30^3 23 -> 13; four columns, 16^3 10.8 -> 8.0; but lines of 8 rows and
+  // 200 columns 11.3, with single wavefronts 12.0).
+  const bool narrow = nodes[0] * std::max(ncols, 1 << cw_log2) <= kNarrowLine;
   if (narrow) wgs = std::min<int64_t>((lines + 3) / 4, 4096);
   hipLaunchKernelGGL(zero_shared_rows_kernel, dim3((unsigned)wgs), dim3(256), 0, s, Y,
                      (int)nodes[0], (int)nodes[1], p, py, last_face_y(nodes, p), ncols, ld, lines,
