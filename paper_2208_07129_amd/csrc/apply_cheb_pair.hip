@@ -128,6 +128,7 @@ apply_cheb_pair_kernel(const GridDesc grid, const double* __restrict__ geo,
     const bool first = cy == cya, last = cy + 1 == cyb;
     {
       const int l = fresh_lane();
+      lds_handover();
 #pragma unroll
       for (int r = 0; r < NPM; ++r)
         if (l + 64 * r < NQ2 * 4)
@@ -135,7 +136,7 @@ apply_cheb_pair_kernel(const GridDesc grid, const double* __restrict__ geo,
 #pragma unroll
       for (int r = 0; r < ND; ++r)
         if (l + 64 * r < NP3) sd[l + 64 * r] = dq[r];
-      __builtin_amdgcn_wave_barrier();
+      lds_handover();
       const int k = l >> 4, kz = min(k, P);
       const double* d0 = sd + kz * (NP * NP);
       const double* d1 = sd + (P - kz) * (NP * NP);

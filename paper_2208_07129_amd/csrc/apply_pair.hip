@@ -108,9 +108,10 @@ apply_pair_kernel(const GridDesc grid, const double* __restrict__ geo,
   for (int cy = cya; cy < cyb; ++cy) {
     {
       const int l = fresh_lane();
+      lds_handover();
 #pragma unroll
       for (int r = 0; r < NPM; ++r) put_pm(pq[r], l + 64 * r);
-      __builtin_amdgcn_wave_barrier();
+      lds_handover();
       const int slot = l & (kPairCols - 1);
       c.contract(&pms[min(slot / B, LX - 1)][l >> 4], g0, g1, g2);
     }

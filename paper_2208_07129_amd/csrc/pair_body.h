@@ -117,6 +117,14 @@ __device__ __forceinline__ void pin(double (&v)[2][N][N]) {
 }
 __device__ __forceinline__ void stage_end() { __builtin_amdgcn_sched_barrier(0); }
 
+// Between LDS accesses of different lanes of the wavefront to the same places: keeps the
+// stores before it in front of the reads behind it and the reads before it in front of
+// the stores behind it.  Nothing is emitted, as a wavefront's LDS accesses execute in order.
+__device__ __forceinline__ void lds_handover() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // The lane number, recomputed where it is used: what depends on it is not held
 // in registers across the cells of a segment.
 __device__ __forceinline__ int fresh_lane() {
