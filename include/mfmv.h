@@ -215,8 +215,10 @@ int mf_zero(double* Y, int64_t nrows, int ncols, int64_t ld, void* stream);
  * in this precision (it takes effect unless mf_set_launch(_mixed) sets a shape:
  * mf_tune clears that setting).
  *   cache_path: a JSON file (NULL: no cache) of entries
- *     "<arch>/p<p>q<q>/cells<E>/nvec<nvec>/<fp64|fp32|bf16>":
- *       {"cfg": <shape>, "ms": [median ms per shape, -1 if not timed]};
+ *     "<arch>/p<p>q<q>/cells<E>/nvec<nvec>/<fp32|bf16>" or
+ *     "<arch>/shapes<S>/n<nx>x<ny>x<nz>/p<p>q<q>/cells<E>/nvec<nvec>/fp64":
+ *       {"cfg": <shape>, "ms": [median ms per shape, -1 if not timed]}
+ *   (S: the set of FP64 shapes, raised when a shape's number changes meaning);
  *   a present entry is used without timing; a new result is added by rewriting
  *   the file through a temporary file and a rename (concurrent writers from
  *   several processes may lose each other's entries, never corrupt the file).

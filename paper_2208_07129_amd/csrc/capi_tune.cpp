@@ -1,6 +1,7 @@
 // Launch-shape tuning of the fused apply (mf_tune) and of batches
 // (mf_batch_tune), with a JSON cache on disk keyed by device architecture,
-// degree, quadrature, cells, columns and precision.
+// degree, quadrature, cells, columns and precision (FP64: also the set of shapes and
+// the cells per direction).
 //
 // The candidate shapes (column tile per workgroup, columns per thread,
 // threads, one-shot or persistent grid) play the part of the paper's sweep of
@@ -185,9 +186,15 @@ int mf_tune(mf_operator* handle, int nvec, int prec, const char* cache_path) {
       if (apply_mixed_supported(op->p, op->q, c)) cand.push_back(c);
   }
   if (cand.size() < 2) return MF_OK;
-  char kb[160];
-  std::snprintf(kb, sizeof(kb), "p%dq%d/cells%lld/nvec%d/%s", op->p, op->q, (long long)op->ncells,
-                nvec, prec_name(prec));
+  // FP64 shapes depend on the extents (shape 0 marches along y over groups of cells in x)
+  // and are numbered by kBoxShapeSet; an entry of another set names other kernels, or was
+  // chosen without them, and is not taken.
+  char kb[200], box[80] = "";
+  if (!mixed)
+    std::snprintf(box, sizeof(box), "shapes%d/n%dx%dx%d/", kBoxShapeSet, op->grid.n[0],
+                  op->grid.n[1], op->grid.n[2]);
+  std::snprintf(kb, sizeof(kb), "%sp%dq%d/cells%lld/nvec%d/%s", box, op->p, op->q,
+                (long long)op->ncells, nvec, prec_name(prec));
   const std::string key = arch_prefix() + kb;
   int& override_cfg = mixed ? op->mcfg : op->cfg;
   override_cfg = -1;  // the tuned choice applies from now on

@@ -19,6 +19,7 @@ constexpr int kMaxQExtra = 3;  // q in [p+1, p+3]
 // 10 the FP64 matrix-core body (q = p + 1 <= 8)
 constexpr int kBoxMfmaCfg = 10;
 constexpr int kBoxCfgs = 13;
+constexpr int kBoxShapeSet = 2;  // raised whenever a shape's number comes to mean another kernel
 constexpr int kMfmaMaxN = 8;     // points per direction the matrix-core body handles
 constexpr int kMixedCfgs = 7;  // launch shapes of the mixed-precision apply (4..6: FP32 vector)
 constexpr int kBatchCfgs = 6;  // launch shapes of the batched apply (3..5: one launch per kind)
