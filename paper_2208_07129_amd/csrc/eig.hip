@@ -409,7 +409,7 @@ bj_pair_kernel(int K, int r, const double* __restrict__ Aw, double* __restrict__
 // rows 64 rb .. 64 rb + 63 of V in the columns of pair j, replaced by
 // piece J_j.  The pieces are disjoint, so the update is in place.
 // Bound by the LDS reads of the products (6 bytes per multiply-add); 512 threads
-// instead of 256 hide more of the loads: 24 -> 16.5 us at K = 256.
+// instead of 256 hide more of the loads: 24 -> 18 us at K = 256.
 constexpr int kBjUpdThreads = 512;
 __global__ void __launch_bounds__(kBjUpdThreads)
 bj_update_kernel(int K, int r, double* __restrict__ Aw, double* __restrict__ Vw,

@@ -385,7 +385,7 @@ __device__ inline int cell_node_factor(const GridDesc& g, int np, int cx, int cy
 // of 8 k rows of B and permutes them to runs of k, which leaves it with columns
 // NB c .. NB c + NB - 1 of C (c = lane % 16): one store per row, 64 NB bytes of
 // FP32 in a run.  Bound by memory; 344 x 1024000 x 344, FP32 out, cell-blocked
-// (2.1 GB): 500 us, 4.2 TB/s; the tiled kernel below takes 980.
+// (2.1 GB): 500 us, 4.2 TB/s; the tiled kernel above takes 980.
 // 256 x 128000 x 344, bias, ReLU, BF16 out: 45 us (72 tiled).
 // The epilogue is a template parameter and its stores are dropped past the edge
 // by the buffer's bound: with a branch the count of stores in flight is unknown
@@ -1213,7 +1213,9 @@ bool gemm_far(bool ta, bool tb, int64_t lda, int64_t ldb, int kb) {
 
 // The epilogue with which the one-pass kernel can take a product (-1: it cannot): the one
 // place where its limits stand, for the dispatch and for the callers that need it (the
-// tiled kernel knows no targets).
+// tiled kernel knows no targets).  K: the operands of the networks up to degree 6 (344
+// and, with 256 hidden values, 600), 11 x 4 or 19 x 2 runs of k in a lane's registers;
+// longer ones were not built.
 int wide_epi(int M, int N, int K, bool ta, bool tb, int64_t lda, int64_t ldb, const GemmEpi& ep) {
   const GemmVec vec = gemm_vec(ep);
   if (tb || ep.atomic || N < kWideMinN || M > kWideMaxM || K > (ta ? 352 : 608)) return -1;

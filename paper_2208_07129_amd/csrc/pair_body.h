@@ -35,6 +35,8 @@
 // it wait for its additions.  Apply with zero fill: 506 (box kernel) -> 418 us;
 // p = 4, 24^3: 585 -> 460; p = 2, 32^3: 455 -> 247; p = 6, 20^3, 128 columns:
 // 1.90 -> 1.50 ms.
+// By the counters the one wavefront per SIMD issues an instruction in 43% of its
+// cycles, waits for a result or an issue slot in 40% and for memory in 17%.
 #pragma once
 
 #include "mf_internal.h"
