@@ -260,12 +260,10 @@ gemm_bf16_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
   }
 
   // D layout of the 16 x 16 tile: lane -> column lane % 16, rows 4 (lane / 16) + r;
-  // rows are m with TB, n otherwise
-  auto post = [&](float v, float bias) {
-    if (ep.bias) v += bias;
-    if (ep.relu) v = v > 0.f ? v : 0.f;
-    return v;
-  };
+  // rows are m with TB, n otherwise.  The bias is loaded and added inside its branch: a load
+  // whose value is chosen behind the branch puts its wait there, and with it one for
+  // every store and addition so far, also where there is no bias (344 x 65536 x 32 with B
+  // transposed 22.1 -> 19.7 us, 1024 x 131072 x 128 303 -> 265).
   if constexpr (TB) {
 #pragma unroll
     for (int i = 0; i < W; ++i)
@@ -276,7 +274,9 @@ gemm_bf16_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
           const int m = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
           const int n = n0 + wn + j * 16 + (lane & 15);
           if (m >= M || n >= N) continue;
-          float x = post(acc[i][j][r], ep.bias ? ep.bias[m] : 0.f);
+          float x = acc[i][j][r];
+          if (ep.bias) x += ep.bias[m];
+          if (ep.relu) x = x > 0.f ? x : 0.f;
           if (ep.mask && !(bf16_to_f32(ep.mask[(int64_t)m * ep.ldmask + n]) > 0.f)) x = 0.f;
           if (ep.out_f32) {
             float* o = ep.out_f32 + (int64_t)m * ep.ld_f32 + n;
@@ -298,10 +298,16 @@ gemm_bf16_kernel(int M, int N, int K, const uint16_t* __restrict__ A, int64_t ld
       for (int i = 0; i < W; ++i) {
         const int m = m0 + wm + i * 16 + (lane & 15);
         if (m >= M) continue;
-        const float bias = ep.bias ? ep.bias[m] : 0.f;
-        f32x4 x;
+        f32x4 x = acc[i][j];
+        if (ep.bias) {
+          const float bias = ep.bias[m];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = post(acc[i][j][r], bias);
+          for (int r = 0; r < 4; ++r) x[r] += bias;
+        }
+        if (ep.relu) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[r] = x[r] > 0.f ? x[r] : 0.f;
+        }
         if (ep.mask) {
           const uint16_t* q = ep.mask + (int64_t)m * ep.ldmask + n;
           ushort4 h;
