@@ -58,7 +58,7 @@ constexpr int kKStep = 32, kPad = 40;  // LDS rows of 80 bytes
 // reads meet on a bank.  Without TB the matrix instruction takes B as its first
 // operand, so a lane holds four consecutive columns of C and stores 16 bytes.
 //
-// 344 x 600 x 128000 (TB, 16 pieces of K): 131 us, 403 TFLOP/s (64 x 64 tiles with
+// 344 x 600 x 128000 (TB, 16 pieces of K): 124 us, 426 TFLOP/s (64 x 64 tiles with
 // element-wise transposing stores and loads selected after they arrive: 250).
 struct GemmVec {  // whether the tiled kernel's outputs take 4-element stores and its mask 4-element loads
   int f32, bf16, mask;
@@ -1253,37 +1253,44 @@ hipError_t launch_gemm_bf16(int M, int N, int K, bool ta, bool tb, const uint16_
   auto tiles_of = [&](int t) { return ((int64_t)N + t - 1) / t * (((int64_t)M + t - 1) / t); };
   // Tiles of 128 halve the LDS reads of a product, tiles of 64 give four times the
   // workgroups, which is what counts while K is short or the tiles are few.  Measured, us
-  // with 64 and with 128: 344 x 31000, K = 128 15.8 / 17.5, 344 38 / 33; 1024 x 8192 x 344, FP32
-  // out 7 % for 128, ReLU and BF16 out 5 % against it, K = 512 17 % and 5 % for it; 1024 x
-  // 32768 x 32 32 / 34, with TB 32 / 45.  A transposed operand costs a tile of 128 more: 1024
-  // x 16384 with the mask, K = 512 13 % against 128, 1024 6 % for it.  Half a tile of rows
-  // or columns is idle below 65 (64 x 131072 x 600 40.5 / 43.7).
+  // with 64 and with 128, at 512 and more tiles of 128: plain FP32 out, K = 256 20.9 / 19.1 (344 x
+  // 31000) and 16.2 / 15.1 (256 x 32768), K = 128 15.8 / 17.5; 64 over 128, BF16 out: 0.98 to 1.08 at
+  // K = 416 and 1.03 to 1.16 at 512 (344 x 31000: 1.26); B transposed: 0.95 to 1.15 at 512 and 1.07
+  // to 1.28 at 600; the mask: 0.88 to 1.10 at 512, 0.89 to 1.14 at 600 and 1.06 to 1.33 at 1024.
+  // Some 350 tiles are enough for a longer K (344 x 16384, 384 tiles: FP32 out, K = 512 20.6 / 19.2;
+  // K = 2048, mask 1.20, B transposed 1.10).  Half a tile is idle below 65 rows or columns (64 x 131072:
+  // K = 600 with B transposed 40.8 / 45.9, 1024 70 / 75).
   // Long pieces of a split K range: once the pieces fill most of the CUs, as one round of
-  // 128-row tiles (131 us with pieces of 8192) then takes less than the several of the
-  // others (344 x 600 x 128000, 240 tiles of 128: 146 / 131; 256 x 344 x 262144, 192: 148 /
-  // 154; 256 x 256 x 128000, 64: 70 / 130).  The pieces are the caller's: each adds its
-  // FP32 sum once, so another cut would round the results differently.
-  constexpr int kFill = 480, kFillSplit = 224, kLongPiece = 4096;
+  // 128-row tiles (114 us with pieces of 8192) then takes less than the several of the
+  // others (344 x 600 x 128000, 240 tiles of 128: 145 / 124; 512 x 768 x 65536, 192: 105 / 116; 256 x
+  // 256 x 128000, 64: 66 / 113).  The pieces are the caller's: each adds its FP32 sum once, so
+  // another cut would round the results differently.
+  constexpr int kFill = 480, kFillLong = 350, kFillSplit = 224, kLongPiece = 4096;
   const bool far = gemm_far(ta, tb, lda, ldb, ep.kb);
-  const bool big = !far && M > 64 && N > 64 &&
-                   (split && kchunk >= kLongPiece
-                        ? tiles_of(128) * kz >= kFillSplit
-                        : tiles_of(128) * kz >= kFill && kchunk >= (ta || tb ? 1024 : ep.out_bf16 ? 448 : 320));
+  const bool plain = !ta && !tb && !ep.out_bf16;
+  const int64_t tiles = tiles_of(128) * kz;
+  const bool big =
+      !far && M > 64 && N > 64 &&
+      (split && kchunk >= kLongPiece
+           ? tiles >= kFillSplit
+           : tiles >= (kchunk >= (plain ? 512 : 1024) ? kFillLong : kFill) &&
+                 kchunk >= (ta || tb ? 576 : plain ? 256 : 448));
   const int64_t total = tiles_of(big ? 128 : 64) * kz;
   const dim3 grid((unsigned)((total + kXcds - 1) / kXcds * kXcds));
   // A long batch takes the one-pass kernel, with 128 columns per workgroup as soon
   // as that gives every CU one (256 x 32768 x 344: 26 us, tiled 30; 16384 columns:
   // 22.6 and 21.8), with 256 from twice as many on (128000 columns: 45 us, 48 with
   // 128; 65536: 35 and 34).  Where its 16-row steps hold too little work for their
-  // barrier and loads, the tiled kernel (tiles of 64) stays ahead: few rows (32 x 65536 x
-  // 32: tiled 6.3, one-pass 7.0), many rows at a short K (1024 x 32768 x 32, ReLU: 27 /
-  // 30), and the mask, which a step loads just before it needs it (M x 32768, M = 256, K =
-  // 32 12 / 17, K = 256 19 / 22, K = 344 even; 65536 columns, K = 64 22 / 24, K = 128 even).
+  // barrier and loads, the tiled kernel stays ahead: few rows at a short K (32 x 65536,
+  // K = 32: tiled 6.3, one-pass 7.0; K = 128 7.5 and 6.4), 512 to 1024 rows of 32768 columns
+  // at K <= 64 (ReLU 27 and 30), with BF16 out 2048 too (52 and 61; FP32 69 and 55), and
+  // the mask, which a step loads just before it needs it (256 x 32768, K = 32 12 and 17,
+  // K = 256 19 and 22, K = 344 even; 65536 columns, K = 64 22 and 24, with 1024 rows 112 and 93).
   const int epi = wide_epi(M, N, K, ta, tb, lda, ldb, ep);
   if (ep.target && epi < 0) return hipErrorInvalidValue;
-  const bool few = M <= 32 && N < 4 * kWideMinN;
-  const bool thin = ta ? (N < 2 * kWideMinN && K <= 256) || (N < 4 * kWideMinN && K < 128)
-                       : N < 2 * kWideMinN && M >= 512 && K <= 64;
+  const bool few = M <= 32 && K <= 96 && N < 4 * kWideMinN;
+  const bool thin = ta ? (N < 2 * kWideMinN && K <= 256) || (N < 4 * kWideMinN && K < 128 && M <= 512)
+                       : N < 2 * kWideMinN && M >= 512 && M <= (ep.out_bf16 ? 2048 : 1024) && K <= 64;
   if (epi >= 0 && (ep.target || !(few || thin))) {
     auto wide = [&](auto ksc, auto nbc, auto tac) {
       constexpr int KS = decltype(ksc)::value, NB = decltype(nbc)::value;
